@@ -111,7 +111,7 @@ struct Batch {
     double *Ha, *Hb;        // [B][Na][Na], [B][Nb][Nb] string Hamiltonians (SIGMA_STRIP; Ha == Hb when na == nb)
     int nblk;               // blocks per tuple for vector kernels
     double *part;           // [B][nblk + 1][kParts] block partial sums (the last block: P-space corrections)
-    double *G;              // [B][kMaxSpace*kMaxSpace] projected matrix V^T H V of the stored basis
+    double *G;              // [B][kMaxSpace*kMaxSpace] projected matrix Q^T H Q (below)
     // The stored basis V is not orthonormal: V = Q U with Q orthonormal and U
     // upper triangular; R = U^-1 (upper triangular, R[i][j] at i*kMaxSpace+j,
     // entries j >= i used), so Q = V R
@@ -201,11 +201,13 @@ hipError_t launch_sigma(const Batch &b, VecRef c, VecRef sig, double shift, bool
                         hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, hipEvent_t evg, hipEvent_t ev2);
 inline bool sigma_fuses_dots(const Batch &b) { return b.sigma_variant == SIGMA_STRIP; }
 int gemm_blocks(const Batch &b);
-hipError_t launch_update_G(const Batch &b, int nsum, hipStream_t s);
 hipError_t launch_guess(const Batch &b, hipStream_t s);
 hipError_t launch_init_state(const Batch &b, hipStream_t s);
 hipError_t launch_dots(const Batch &b, VecRef y, int nx_extra, hipStream_t s);
-hipError_t launch_iter_head(const Batch &b, hipStream_t s);
+// start of an iteration: the new column of the projected matrix from nsum
+// partial blocks (sd: and the S-dots of k_ritz), its lowest eigenpair, then
+// residual, correction and convergence
+hipError_t launch_iter_head(const Batch &b, int nsum, bool sd, hipStream_t s);
 hipError_t launch_orthonormalize(const Batch &b, hipStream_t s);
 hipError_t launch_finalize(const Batch &b, hipStream_t s);
 size_t sigma_lds_bytes(const ParamLayout &pl);

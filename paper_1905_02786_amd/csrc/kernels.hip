@@ -12,6 +12,7 @@
 //   E_core = E_const + sum_c 2 h_cc + sum_cd [2(cc|dd) - (cd|dc)],
 // over p, q, r, s in A and c in the core C.
 #include "device.h"
+#include "smalleig.h"
 #include "symmetry.h"
 
 namespace mbefci {
@@ -826,214 +827,121 @@ __global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref, int nx_extra
     store_block_partials<MS + 1>(b, t, acc, nx);
 }
 
-// G column m: G[i][m] = G[m][i] = V_i . S_m for i <= m (partial blocks
-// 0 .. nsum-1); with `sd`, the entries i < gemm_dot_first of the GEMM's
-// epilogue come from the S-dots of k_ritz instead.  Then m += 1.
-__global__ void k_update_G(Batch b, int nsum, int sd) {
-    const int t = blockIdx.x;
-    if (b.status[t] != ST_RUNNING) return;
-    const int m = b.m[t];
-    double *G = b.G + (int64_t)t * kMaxSpace * kMaxSpace;
-    const int i0 = sd ? gemm_dot_first(b, t, m) : 0;
-    if ((int)threadIdx.x <= m) {
-        double v = 0.0;
-        if ((int)threadIdx.x < i0) v = b.sdot[(int64_t)t * kMaxSpace + threadIdx.x];
-        else
-            for (int blk = 0; blk < nsum; ++blk) v += parts(b, t, blk)[threadIdx.x];
-        G[threadIdx.x * kMaxSpace + m] = v;
-        G[m * kMaxSpace + threadIdx.x] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) b.m[t] = m + 1;
-}
-
 hipError_t launch_dots(const Batch &b, VecRef y, int nx_extra, hipStream_t s) {
     if (b.max_space <= 12) hipLaunchKernelGGL(k_dots<12>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra, 0);
     else hipLaunchKernelGGL(k_dots<kMaxSpace>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra, 0);
-    if (nx_extra == 1) hipLaunchKernelGGL(k_update_G, dim3(b.B), dim3(64), 0, s, b, b.nblk, 0);
     return hipGetLastError();
 }
 
-hipError_t launch_update_G(const Batch &b, int nsum, hipStream_t s) {
-    hipLaunchKernelGGL(k_update_G, dim3(b.B), dim3(64), 0, s, b, nsum, 1);
-    return hipGetLastError();
-}
-
-// Lowest eigenpair of the m x m projected matrix by cyclic Jacobi with a
-// parallel (round-robin) rotation order; one block of 64 threads per tuple.
-// The Jacobi matrix is the projection on the orthonormal basis Q = V R,
-// R^T G R (upper triangle computed, mirrored); its eigenvector y becomes the
-// coefficients R y on the stored basis.  Block 0 also clears the iteration's
-// counters (running tuples, explicit Gram-Schmidt passes), which k_converge
-// and k_coef1 count after it: no memset node in the iteration's launches.
-__global__ __launch_bounds__(64) void k_small_eig(Batch b) {
-    const int t = blockIdx.x;
-    if (t == 0 && threadIdx.x < 2) b.counter[threadIdx.x] = 0;
+// Start of an iteration, one wave per tuple: the projected matrix gains the
+// column of the vector whose sigma was formed last, and its lowest eigenpair
+// gives the Ritz vector's coefficients.
+//
+// b.G holds the projection B = R^T (V^T H V) R on the orthonormal basis Q =
+// V R.  With g_i = V_i . S_m (partial blocks 0 .. nsum-1; with `sd` the
+// entries i < gemm_dot_first from the S-dots of k_ritz instead), c and s of
+// k_coef1 (column m of R is (-R c, 1) s; c = 0 after the explicit passes):
+//   B_im = s ((R^T g)_i - (B c)_i),  B_mm = s^2 (c . B c - 2 c . R^T g + g_m).
+// Block 0 also clears the iteration's counters (running tuples, explicit
+// Gram-Schmidt passes), which k_converge and k_coef1 count after it: no
+// memset node in the iteration's launches.
+template <int MS>
+__global__ __launch_bounds__(64) void k_small_eig(Batch b, int nsum, int sd) {
+    const int t = blockIdx.x, lane = threadIdx.x;
+    if (t == 0 && lane < 2) b.counter[lane] = 0;
     const int32_t st0 = b.status[t];
     if (st0 != ST_RUNNING && st0 != ST_RESTART) return;
-    __syncthreads();
-    if (threadIdx.x == 0 && st0 == ST_RESTART) b.status[t] = ST_RUNNING;
-    const int m = b.m[t];
-    const int mm = m + (m & 1);                  // even number of players
-    __shared__ double A[kMaxSpace + 1][kMaxSpace + 2];
-    __shared__ double Vv[kMaxSpace + 1][kMaxSpace + 2];
-    __shared__ double Rs[kMaxSpace][kMaxSpace + 1];
-    __shared__ double cs[(kMaxSpace + 2) / 2], sn[(kMaxSpace + 2) / 2];
-    __shared__ int pa[(kMaxSpace + 2) / 2], pb[(kMaxSpace + 2) / 2];
-    __shared__ int done;
-    __shared__ double wv[kMaxSpace];
-    const int tid = threadIdx.x;
-    const double *G = b.G + (int64_t)t * kMaxSpace * kMaxSpace;
+    __shared__ SmallEig<MS> q;
+    __shared__ double B[kMaxSpace][kMaxSpace + 1], R[kMaxSpace][kMaxSpace + 1];
+    __shared__ double gv[kMaxSpace], cv[kMaxSpace], wv[kMaxSpace];
+    constexpr int IW = SmallEig<MS>::IW;
+    double *Gg = b.G + (int64_t)t * kMaxSpace * kMaxSpace;
     const double *Rg = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
-    // Rs = R (upper triangle, zero below), Vv = G R, then A = R^T (G R)
-    for (int i = tid; i < m * m; i += 64) {
-        const int r = i / m, c = i % m;
-        Rs[r][c] = (r <= c) ? Rg[r * kMaxSpace + c] : 0.0;
+    int m = b.m[t];
+    const int n = st0 == ST_RUNNING ? m + 1 : m;   // columns of the basis
+    for (int k = lane; k < n * IW; k += 64) {
+        const int r = k / IW, c = k & (IW - 1);
+        if (c < m && r < m) B[r][c] = Gg[r * kMaxSpace + c];
+        if (c < n && r <= c) R[r][c] = Rg[r * kMaxSpace + c];
     }
-    __syncthreads();
-    for (int i = tid; i < m * m; i += 64) {
-        const int r = i / m, c = i % m;
+    if (st0 == ST_RUNNING) {
+        const int i0 = sd ? gemm_dot_first(b, t, m) : 0;
+        const bool two = m > 0 && b.cgs2[t];
+        if (lane < i0) gv[lane] = b.sdot[(int64_t)t * kMaxSpace + lane];
+        for (int c = i0; c <= m; ++c) {
+            double x = 0.0;
+            for (int blk = lane; blk < nsum; blk += 64) x += parts(b, t, blk)[c];
+            x = wave_sum(x);
+            if (lane == 0) gv[c] = x;
+        }
+        if (lane < m) cv[lane] = two ? 0.0 : b.coef[(int64_t)t * kMaxSpace + lane];
+        wave_sync();
+        const double s = R[m][m];
+        double rg = 0.0, bc = 0.0;
+        if (lane < m) {
+            for (int j = 0; j <= lane; ++j) rg += R[j][lane] * gv[j];
+            for (int j = 0; j < m; ++j) bc += B[lane][j] * cv[j];
+        }
+        const double cc = wave_sum(lane < m ? cv[lane] * (bc - 2.0 * rg) : 0.0);
+        wave_sync();
+        const double v = lane < m ? s * (rg - bc) : s * s * (cc + gv[m]);
+        if (lane <= m) {
+            B[lane][m] = B[m][lane] = v;
+            Gg[lane * kMaxSpace + m] = Gg[m * kMaxSpace + lane] = v;
+        }
+        ++m;
+        if (lane == 0) b.m[t] = m;
+    } else if (lane == 0) {
+        b.status[t] = ST_RUNNING;
+    }
+    wave_sync();
+    for (int k = lane; k < m * IW; k += 64) {
+        const int r = k / IW, c = k & (IW - 1);
+        if (c < m) q.A[r][c] = B[r][c];
+    }
+    wave_sync();
+    double z;
+    const double th = lowest_eig<MS>(q, m, z);
+    // coefficients R z on the stored basis
+    if (lane < m) gv[lane] = z;
+    wave_sync();
+    if (lane < m) {
         double v = 0.0;
-        for (int k = 0; k <= c; ++k) v += G[r * kMaxSpace + k] * Rs[k][c];
-        Vv[r][c] = v;
+        for (int j = lane; j < m; ++j) v += R[lane][j] * gv[j];
+        b.y[(int64_t)t * kMaxSpace + lane] = v;
     }
-    __syncthreads();
-    for (int i = tid; i < mm * mm; i += 64) {
-        const int r = i / mm, c = i % mm;
-        if (r <= c) {
-            double v = 0.0;
-            if (c < m)
-                for (int k = 0; k <= r; ++k) v += Rs[k][r] * Vv[k][c];
-            A[r][c] = v;
-            A[c][r] = v;
-        }
-    }
-    __syncthreads();
-    for (int i = tid; i < mm * mm; i += 64) {
-        const int r = i / mm, c = i % mm;
-        Vv[r][c] = (r == c) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    // round-robin schedule: position 0 keeps player 0, positions 1 .. mm-1
-    // rotate by one per round (period mm - 1)
-    auto player = [&](int pos, int round) { return pos == 0 ? 0 : 1 + (pos - 1 + (mm - 1) - round) % (mm - 1); };
-    const int half = mm / 2;
-    // rotation loops: for mm <= 16 item idx is pair idx >> 4, row or column
-    // idx & 15 (no integer division); larger subspaces use idx / mm, idx % mm
-    const bool small = mm <= 16;
-    for (int sweep = 0; sweep < 30; ++sweep) {
-        {
-            // off-diagonal and total squared norms (lane-parallel, fixed order)
-            double off = 0.0, tot = 0.0;
-            for (int i = tid; i < m * m; i += 64) {
-                const int r = i / m, c = i % m;
-                const double a2 = A[r][c] * A[r][c];
-                tot += a2;
-                if (r != c) off += a2;
+    // A restart keeps the Ritz vector and, with restart_keep 2, the previous
+    // iteration's Ritz vector (zp, coordinates of Q, zero past its length)
+    // made orthogonal to it by two passes in these coordinates; kept when that
+    // leaves a norm above 1e-6.  Its coefficients on the stored basis are R w,
+    // its Rayleigh quotient w . B w.  The two are orthonormal and the projected
+    // matrix on them is diag(theta, mu).
+    const bool rs = m >= b.max_space || st0 == ST_RESTART;
+    double *zp = b.zp + (int64_t)t * kMaxSpace;
+    const double zl = lane < m ? z : 0.0;
+    int keep = rs ? 1 : 0;
+    if (rs && b.restart_keep > 1) {
+        double w = lane < m ? zp[lane] : 0.0;
+        for (int pass = 0; pass < 2; ++pass) w -= wave_sum(zl * w) * zl;
+        const double nw = wave_sum(w * w);
+        if (nw > 1e-12) {
+            w *= 1.0 / sqrt(nw);
+            if (lane < m) wv[lane] = w;
+            wave_sync();
+            double bw = 0.0, y2 = 0.0;
+            if (lane < m) {
+                for (int j = 0; j < m; ++j) bw += B[lane][j] * wv[j];
+                for (int j = lane; j < m; ++j) y2 += R[lane][j] * wv[j];
+                b.y2[(int64_t)t * kMaxSpace + lane] = y2;
             }
-            off = wave_sum(off);
-            tot = wave_sum(tot);
-            if (tid == 0) done = (off <= 1e-30 * tot) ? 1 : 0;   // off-diagonal norm <= 1e-15 of the total
-        }
-        __syncthreads();
-        if (done) break;
-        for (int round = 0; round < mm - 1; ++round) {
-            if (tid < half) {
-                int p = player(tid, round), q = player(mm - 1 - tid, round);
-                if (p > q) { const int x = p; p = q; q = x; }
-                double c = 1.0, s = 0.0;
-                if (q < m && A[p][q] != 0.0) {
-                    const double apq = A[p][q];
-                    const double tau = (A[q][q] - A[p][p]) / (2.0 * apq);
-                    const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + tt * tt);
-                    s = tt * c;
-                }
-                cs[tid] = c;
-                sn[tid] = s;
-                pa[tid] = p;
-                pb[tid] = q;
-            }
-            __syncthreads();
-            // columns: A <- A J, V <- V J
-            for (int idx = tid; idx < half * (small ? 16 : mm); idx += 64) {
-                const int k = small ? idx >> 4 : idx / mm, r = small ? idx & 15 : idx % mm;
-                if (r >= mm) continue;
-                const int p = pa[k], q = pb[k];
-                const double c = cs[k], s = sn[k];
-                const double arp = A[r][p], arq = A[r][q];
-                A[r][p] = c * arp - s * arq;
-                A[r][q] = s * arp + c * arq;
-                const double vrp = Vv[r][p], vrq = Vv[r][q];
-                Vv[r][p] = c * vrp - s * vrq;
-                Vv[r][q] = s * vrp + c * vrq;
-            }
-            __syncthreads();
-            // rows: A <- J^T A
-            for (int idx = tid; idx < half * (small ? 16 : mm); idx += 64) {
-                const int k = small ? idx >> 4 : idx / mm, col = small ? idx & 15 : idx % mm;
-                if (col >= mm) continue;
-                const int p = pa[k], q = pb[k];
-                const double c = cs[k], s = sn[k];
-                const double apc = A[p][col], aqc = A[q][col];
-                A[p][col] = c * apc - s * aqc;
-                A[q][col] = s * apc + c * aqc;
-            }
-            __syncthreads();
+            const double mu = wave_sum(w * bw);
+            if (lane == 0) b.mu[t] = mu;
+            keep = 2;
         }
     }
-    if (tid == 0) {
-        int k = 0;
-        for (int i = 1; i < m; ++i)
-            if (A[i][i] < A[k][k]) k = i;
-        b.theta[t] = A[k][k];
-        double *y = b.y + (int64_t)t * kMaxSpace;
-        for (int i = 0; i < m; ++i) {
-            double v = 0.0;
-            for (int j = i; j < m; ++j) v += Rs[i][j] * Vv[j][k];
-            y[i] = v;
-        }
-        // A restart keeps the Ritz vector and, with restart_keep 2, the
-        // previous iteration's Ritz vector (zp, coordinates of Q, zero past
-        // its length) made orthogonal to it by two passes in these
-        // coordinates; kept when that leaves a norm above 1e-6.  Its
-        // Rayleigh quotient comes from the eigen-decomposition of the
-        // projected matrix (A's diagonal, eigenvectors Vv), its coefficients
-        // on the stored basis are R w.  The two are orthonormal and the
-        // projected matrix on them is diag(theta, mu).
-        const bool rs = m >= b.max_space || st0 == ST_RESTART;
-        double *zp = b.zp + (int64_t)t * kMaxSpace;
-        int keep = rs ? 1 : 0;
-        if (rs && b.restart_keep > 1) {
-            for (int i = 0; i < m; ++i) wv[i] = zp[i];
-            for (int pass = 0; pass < 2; ++pass) {
-                double d = 0.0;
-                for (int i = 0; i < m; ++i) d += Vv[i][k] * wv[i];
-                for (int i = 0; i < m; ++i) wv[i] -= d * Vv[i][k];
-            }
-            double nw = 0.0;
-            for (int i = 0; i < m; ++i) nw += wv[i] * wv[i];
-            if (nw > 1e-12) {
-                const double sc = 1.0 / sqrt(nw);
-                for (int i = 0; i < m; ++i) wv[i] *= sc;
-                double mu = 0.0;
-                for (int j = 0; j < m; ++j) {
-                    double cj = 0.0;
-                    for (int i = 0; i < m; ++i) cj += Vv[i][j] * wv[i];
-                    mu += cj * cj * A[j][j];
-                }
-                b.mu[t] = mu;
-                double *y2 = b.y2 + (int64_t)t * kMaxSpace;
-                for (int i = 0; i < m; ++i) {
-                    double v = 0.0;
-                    for (int j = i; j < m; ++j) v += Rs[i][j] * wv[j];
-                    y2[i] = v;
-                }
-                keep = 2;
-            }
-        }
-        if (!rs)
-            for (int i = 0; i < kMaxSpace; ++i) zp[i] = i < m ? Vv[i][k] : 0.0;
+    if (!rs && lane < kMaxSpace) zp[lane] = zl;
+    if (lane == 0) {
+        b.theta[t] = th;
         b.restart[t] = keep;
     }
 }
@@ -1271,12 +1179,14 @@ __global__ void k_coef1(Batch b) {
         return;
     }
     const double s = 1.0 / sqrt(kept);
+    if (i < m) b.coef[(int64_t)t * kMaxSpace + i] = c;   // for the new column of the projected matrix
     if (i < m) R[i * kMaxSpace + m] = -a * s;
     if (i == m) R[m * kMaxSpace + m] = s;
 }
 
-hipError_t launch_iter_head(const Batch &b, hipStream_t s) {
-    hipLaunchKernelGGL(k_small_eig, dim3(b.B), dim3(64), 0, s, b);
+hipError_t launch_iter_head(const Batch &b, int nsum, bool sd, hipStream_t s) {
+    if (b.max_space <= 12) hipLaunchKernelGGL(k_small_eig<12>, dim3(b.B), dim3(64), 0, s, b, nsum, sd ? 1 : 0);
+    else hipLaunchKernelGGL(k_small_eig<kMaxSpace>, dim3(b.B), dim3(64), 0, s, b, nsum, sd ? 1 : 0);
     const bool v2 = (b.dim & 1) == 0;
     if (b.max_space <= 12) {
         if (v2) hipLaunchKernelGGL((k_ritz<12, true>), dim3(b.nblk, b.B), dim3(256), 0, s, b);

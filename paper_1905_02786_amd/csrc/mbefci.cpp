@@ -752,16 +752,17 @@ mbefci_status davidson_batch(mbefci_ctx *ctx, const Batch &b, double *e_out, int
         ++ctx->stats.whole_batches;
         return davidson_finish(ctx, b, e_out, st_out, ro);
     }
-    // sigma of V_m into S_m, then column m of G (from the GEMM's partial dots
-    // where the sigma variant computes them)
-    auto sigma_and_G = [&](int64_t napps) -> mbefci_status {
-        const bool fused = sigma_fuses_dots(b);
+    // sigma of V_m into S_m and the partial dots of the projected matrix's new
+    // column (the GEMM's where the sigma variant computes them)
+    const bool fused = sigma_fuses_dots(b);
+    const int nsum = fused ? gemm_blocks(b) : b.nblk;
+    auto sigma_and_dots = [&](int64_t napps) -> mbefci_status {
         mbefci_status r = run_sigma(ctx, b, vm, sm, 0.0, true, napps, fused);
         if (r != MBEFCI_OK) return r;
-        hipError_t e2 = fused ? launch_update_G(b, gemm_blocks(b), s) : launch_dots(b, sm, 1, s);
+        hipError_t e2 = fused ? hipSuccess : launch_dots(b, sm, 1, s);
         return e2 == hipSuccess ? MBEFCI_OK : ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e2));
     };
-    mbefci_status rc = sigma_and_G(b.B);
+    mbefci_status rc = sigma_and_dots(b.B);
     if (rc != MBEFCI_OK) return rc;
     int32_t cnt[3] = {b.B, 0, 0};   // running tuples; of them those that need the explicit Gram-Schmidt
                                     // passes; explicit passes of the whole batch
@@ -771,14 +772,14 @@ mbefci_status davidson_batch(mbefci_ctx *ctx, const Batch &b, double *e_out, int
         // iteration is timed with events, and the explicit Gram-Schmidt
         // passes are launched only when some tuple needs them
         for (int it = 0; it <= b.max_iter; ++it) {
-            if ((e = launch_iter_head(b, s)) != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
+            if ((e = launch_iter_head(b, nsum, fused, s)) != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
             HIPCHK(hipMemcpyAsync(cnt, b.counter, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             flush_sigma_time(ctx);
             if (cnt[0] == 0) break;
             if (cnt[1] > 0 && (e = launch_orthonormalize(b, s)) != hipSuccess)
                 return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
-            rc = sigma_and_G(cnt[0]);
+            rc = sigma_and_dots(cnt[0]);
             if (rc != MBEFCI_OK) return rc;
         }
     } else {
@@ -789,14 +790,13 @@ mbefci_status davidson_batch(mbefci_ctx *ctx, const Batch &b, double *e_out, int
         // iteration per round trip.  With options.graph the iteration's
         // launches are captured once per batch in a hipGraph (on a private
         // stream) and the graph is replayed on the context's stream.
-        const bool fused = sigma_fuses_dots(b);
         auto one_iter = [&](hipStream_t st) -> hipError_t {
-            hipError_t e1 = launch_iter_head(b, st);
+            hipError_t e1 = launch_iter_head(b, nsum, fused, st);
             if (e1 != hipSuccess) return e1;
             if ((e1 = launch_orthonormalize(b, st)) != hipSuccess) return e1;
             if ((e1 = launch_sigma(b, vm, sm, 0.0, true, fused, st, nullptr, nullptr, nullptr, nullptr)) != hipSuccess)
                 return e1;
-            return fused ? launch_update_G(b, gemm_blocks(b), st) : launch_dots(b, sm, 1, st);
+            return fused ? hipSuccess : launch_dots(b, sm, 1, st);
         };
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;

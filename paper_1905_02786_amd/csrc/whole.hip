@@ -18,6 +18,7 @@
 // kernels apply.  On exit theta, status, iteration count, m and the Ritz
 // coefficients y on V are written as the batched iteration leaves them.
 #include "device.h"
+#include "smalleig.h"
 #include "symmetry.h"
 
 namespace mbefci {
@@ -30,20 +31,19 @@ constexpr int kWholeMaxLds = 160 * 1024;
 
 struct WholeShared {
     double G[kMaxSpace][kWholeLd];      // projected matrix on the orthonormal basis
-    double A[2][kMaxSpace][kWholeLd];   // Jacobi iterates (rounds alternate between the two)
-    double Z[kMaxSpace][kWholeLd];      // eigenvectors of G in the columns (kept for a warm start)
-    double W[kMaxSpace][kWholeLd];      // scratch of the warm start
     double red[kWholeWaves][kWholeRed];
     double sum[kWholeRed];
     double y[kMaxSpace], yp[kMaxSpace], z[kMaxSpace];
     double pr[kPsp], pw[kPsp], pc[kPsp];
     double pd[kPsp], pe[kPsp];   // diagonal and subdiagonal of the P-space tridiagonal factor
-    unsigned short pairs[kMaxSpace - 1][kMaxSpace / 2];   // Jacobi round-robin pairs (p | q << 8)
-    double rc[kMaxSpace / 2], rs[kMaxSpace / 2];          // the round's rotations
     double pp[kWholeThreads / kPsp][kPsp];   // partial sums of the P-space products
     double theta, mu;
     int done, keep, cur;
 };
+
+// LDS set aside for the static part of k_whole
+constexpr size_t kWholeStatic = 55952;
+static_assert(sizeof(WholeShared) + sizeof(SmallEig<kMaxSpace>) <= kWholeStatic, "static LDS of k_whole");
 
 // Dynamic LDS: the vector of the current sigma, the pair integrals, the
 // string Hamiltonians (one when both spins have the same electron count) and
@@ -55,7 +55,7 @@ size_t whole_lds_bytes(const ParamLayout &pl, int64_t dim, int64_t Na, int64_t N
 
 bool whole_fits(const ParamLayout &pl, int64_t dim, int64_t Na, int64_t Nb, int nentA, int nentB, bool same) {
     return pl.nA <= kWholeMaxActive && dim <= kWholeMaxDim && nentB <= kWholeMaxNent && nentA <= kWholeMaxNent &&
-           whole_lds_bytes(pl, dim, Na, Nb, nentA, nentB, same) + sizeof(WholeShared) <= (size_t)kWholeMaxLds;
+           whole_lds_bytes(pl, dim, Na, Nb, nentA, nentB, same) + kWholeStatic <= (size_t)kWholeMaxLds;
 }
 
 // Sums over the workgroup of acc[0 .. n-1] into w.sum[0 .. n-1] and, with
@@ -87,170 +87,23 @@ __device__ __forceinline__ void wg_sums(WholeShared &w, const double (&acc)[N], 
     __syncthreads();
 }
 
-// Ordering point between the phases of the single wave that runs the small
-// eigenproblem: a wave executes its LDS operations in order, so only the
-// compiler has to be kept from moving LDS accesses across this point.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Reciprocal and reciprocal square root: the hardware approximations refined
-// by two Newton steps (to a few ulps; used for the rotations of the small
-// eigenproblem and the pivots of the P-space solve).
-__device__ __forceinline__ double fast_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
-}
-__device__ __forceinline__ double fast_rsq(double x) {
-    double r = __builtin_amdgcn_rsq(x);
-    r = r * fma(-0.5 * x * r, r, 1.5);
-    return r * fma(-0.5 * x * r, r, 1.5);
-}
-
-// Lowest eigenpair of the symmetric m x m matrix w.G by cyclic Jacobi
-// rotations, run by the first wave (the others wait at the workgroup barrier
-// at the end).  The pairs of a round are disjoint (round-robin order, one
-// dummy index when m is odd): the lanes first form the round's rotations,
-// then apply all of them at once, each lane a fixed set of 2 x 2 blocks of
-// J^T A J (A read from one buffer, written to the other) and rows of Z J.
-// Warm start: w.Z holds the eigenvectors of the leading zm x zm block of G
-// (the previous iteration's projected matrix), so the iteration starts from
-// Z_ext^T G Z_ext, Z_ext = diag(Z, I), which is diagonal but for its new rows
-// and columns.  Leaves w.theta, w.y (zero past m) and the eigenvectors in w.Z.
+// Lowest eigenpair of the symmetric m x m matrix w.G, by the first wave (the
+// others wait at the workgroup barrier at the end): w.theta, and w.y (zero
+// past m).
 template <int MS>
-__device__ void wg_lowest_eig(WholeShared &w, int m, int zm) {
-    const int tid = threadIdx.x, mm = m + (m & 1), half = mm / 2;
+__device__ __forceinline__ void wg_lowest_eig(WholeShared &w, SmallEig<MS> &q, int m) {
+    constexpr int IW = SmallEig<MS>::IW;
+    const int tid = threadIdx.x;
     if (tid < 64) {
-        for (int i = tid; i < mm * mm; i += 64) {
-            const int r = i / mm, c = i - r * mm;
-            w.W[r][c] = (r < zm && c < zm) ? w.Z[r][c] : (r == c ? 1.0 : 0.0);
-        }
-        // round r pairs position 0 with position mm - 1 and position k with
-        // mm - 1 - k; the indices at positions 1 .. mm-1 rotate by one per round
-        for (int i = tid; i < (mm - 1) * half; i += 64) {
-            const int round = i / half, k = i - round * half;
-            auto at = [&](int pos) { return pos == 0 ? 0 : 1 + (pos - 1 + round) % (mm - 1); };
-            const int a = at(k), c = at(mm - 1 - k);
-            w.pairs[round][k] = (unsigned short)((a < c ? a : c) | ((a < c ? c : a) << 8));
+        for (int k = tid; k < m * IW; k += 64) {
+            const int r = k / IW, c = k & (IW - 1);
+            if (c < m) q.A[r][c] = w.G[r][c];
         }
         wave_sync();
-        for (int i = tid; i < mm * mm; i += 64) {   // Z <- G Z_ext (scratch)
-            const int r = i / mm, c = i - r * mm;
-            double v = 0.0;
-            if (r < m && c < m)
-                for (int k = 0; k < m; ++k) v += w.G[r][k] * w.W[k][c];
-            w.Z[r][c] = v;
-        }
-        wave_sync();
-        for (int i = tid; i < mm * mm; i += 64) {   // A = Z_ext^T G Z_ext (upper, mirrored)
-            const int r = i / mm, c = i - r * mm;
-            if (r <= c) {
-                double v = 0.0;
-                if (c < m)
-                    for (int k = 0; k < m; ++k) v += w.W[k][r] * w.Z[k][c];
-                w.A[0][r][c] = v;
-                w.A[0][c][r] = v;
-            }
-        }
-        wave_sync();
-        for (int i = tid; i < mm * mm; i += 64) {
-            const int r = i / mm, c = i - r * mm;
-            w.Z[r][c] = w.W[r][c];
-        }
-        // this lane's items of a round: blocks (k, k2) of A, then rows r of Z
-        // for pair k (bit 15 set), indices packed 5 bits each
-        constexpr int NI = ((MS / 2) * (MS / 2) + (MS / 2) * MS + 63) / 64;
-        const int nblk = half * half, nitem = nblk + half * mm;
-        int item[NI];
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int i = tid + 64 * j;
-            int v = -1;
-            if (i < nblk) v = ((i / half) << 5) | (i % half);
-            else if (i < nitem) v = 0x8000 | (((i - nblk) / mm) << 5) | ((i - nblk) % mm);
-            item[j] = v;
-        }
-        wave_sync();
-        int cur = 0;
-        for (int sweep = 0; sweep < 30 && mm > 1; ++sweep) {
-            double off = 0.0, tot = 0.0;
-            if (tid < m)
-                for (int r = 0; r < m; ++r) {
-                    const double a = w.A[cur][r][tid];
-                    tot += a * a;
-                    if (r != tid) off += a * a;
-                }
-            off = wave_sum(off);
-            tot = wave_sum(tot);
-            if (off <= 1e-24 * tot) break;   // the same sums in every lane
-            for (int round = 0; round < mm - 1; ++round) {
-                const double (&Ai)[kMaxSpace][kWholeLd] = w.A[cur];
-                if (tid < half) {
-                    // the rotation that zeroes A[p][q]: t = tan of its angle,
-                    // the smaller root of t^2 + 2 tau t - 1 = 0 (identity for
-                    // the dummy index and for a zero entry)
-                    const unsigned pk = w.pairs[round][tid];
-                    const int p = pk & 255, q = pk >> 8;
-                    const double apq = Ai[p][q];
-                    double c = 1.0, s = 0.0;
-                    if (q < m && apq != 0.0) {
-                        const double tau = (Ai[q][q] - Ai[p][p]) * fast_rcp(2.0 * apq);
-                        const double at = fabs(tau);
-                        double tt;
-                        if (at > 1e150) tt = 0.5 * fast_rcp(tau);
-                        else {
-                            const double u = fma(tau, tau, 1.0);
-                            tt = fast_rcp(at + u * fast_rsq(u));
-                            if (tau < 0.0) tt = -tt;
-                        }
-                        c = fast_rsq(fma(tt, tt, 1.0));
-                        s = tt * c;
-                    }
-                    w.rc[tid] = c;
-                    w.rs[tid] = s;
-                }
-                wave_sync();
-                double (&Ao)[kMaxSpace][kWholeLd] = w.A[cur ^ 1];
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int v = item[j];
-                    if (v < 0) continue;
-                    if (!(v & 0x8000)) {
-                        // block (pair k rows, pair k2 columns) of J^T A J
-                        const int k = v >> 5, k2 = v & 31;
-                        const unsigned pk = w.pairs[round][k], pk2 = w.pairs[round][k2];
-                        const int p = pk & 255, q = pk >> 8, p2 = pk2 & 255, q2 = pk2 >> 8;
-                        const double c = w.rc[k], s = w.rs[k], c2 = w.rc[k2], s2 = w.rs[k2];
-                        const double xpp = c2 * Ai[p][p2] - s2 * Ai[p][q2], xpq = s2 * Ai[p][p2] + c2 * Ai[p][q2];
-                        const double xqp = c2 * Ai[q][p2] - s2 * Ai[q][q2], xqq = s2 * Ai[q][p2] + c2 * Ai[q][q2];
-                        Ao[p][p2] = c * xpp - s * xqp;
-                        Ao[q][p2] = s * xpp + c * xqp;
-                        Ao[p][q2] = c * xpq - s * xqq;
-                        Ao[q][q2] = s * xpq + c * xqq;
-                    } else {
-                        const int k = (v >> 5) & 31, r = v & 31;   // row r of Z J, pair k
-                        const unsigned pk = w.pairs[round][k];
-                        const int p = pk & 255, q = pk >> 8;
-                        const double c = w.rc[k], s = w.rs[k];
-                        const double zp = w.Z[r][p], zq = w.Z[r][q];
-                        w.Z[r][p] = c * zp - s * zq;
-                        w.Z[r][q] = s * zp + c * zq;
-                    }
-                }
-                cur ^= 1;
-                wave_sync();
-            }
-        }
-        if (tid == 0) {
-            int k = 0;
-            for (int i = 1; i < m; ++i)
-                if (w.A[cur][i][i] < w.A[cur][k][k]) k = i;
-            w.theta = w.A[cur][k][k];
-            for (int i = 0; i < kMaxSpace; ++i) w.y[i] = i < m ? w.Z[i][k] : 0.0;
-        }
+        double y;
+        const double th = lowest_eig<MS>(q, m, y);
+        if (tid < kMaxSpace) w.y[tid] = tid < m ? y : 0.0;
+        if (tid == 0) w.theta = th;
     }
     __syncthreads();
 }
@@ -264,6 +117,7 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(Batch b) {
     const int Kpad = pl.Kpad;
     const bool same = b.Ha == b.Hb;
     __shared__ WholeShared w;
+    __shared__ SmallEig<MS> eig;
     extern __shared__ double wlds[];
     double *cL = wlds;                                    // [dim] vector of the current sigma
     double *eri = cL + ((dim + 1) & ~int64_t(1));         // [P][Kpad] (P|Q) / 2
@@ -373,11 +227,10 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(Batch b) {
         }
         __syncthreads();
     }
-    int m = 1, zm = 0, iter = 0, status = ST_RUNNING, force = 0;
+    int m = 1, iter = 0, status = ST_RUNNING, force = 0;
     double theta_prev = 1e300, theta = 0.0;
     while (true) {
-        wg_lowest_eig<MS>(w, m, zm);
-        zm = m;
+        wg_lowest_eig<MS>(w, eig, m);
         theta = w.theta;
         const bool restart = m >= maxs || force;
         force = 0;
@@ -456,19 +309,15 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(Batch b) {
         const double rn = sqrt(w.sum[0]);
         if (restart) {
             m = keep;
-            zm = keep;   // G = diag(theta, mu): its eigenvectors are the unit vectors
             if (tid == 0) {
                 for (int i = 0; i < kMaxSpace; ++i) {
                     w.y[i] = i == 0 ? 1.0 : 0.0;
                     w.yp[i] = w.y[i];
                 }
                 w.G[0][0] = theta;
-                w.Z[0][0] = 1.0;
                 if (keep == 2) {
                     w.G[0][1] = w.G[1][0] = 0.0;
                     w.G[1][1] = w.mu;
-                    w.Z[0][1] = w.Z[1][0] = 0.0;
-                    w.Z[1][1] = 1.0;
                 }
             }
             __syncthreads();
@@ -635,7 +484,7 @@ hipError_t launch_whole(const Batch &b, hipStream_t s) {
 }
 
 hipError_t init_whole_kernels() {
-    const int dyn = kWholeMaxLds - (int)sizeof(WholeShared);
+    const int dyn = kWholeMaxLds - (int)kWholeStatic;
     hipError_t e = hipFuncSetAttribute((const void *)k_whole<12>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute((const void *)k_whole<kMaxSpace>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
