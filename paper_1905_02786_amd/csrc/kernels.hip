@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) void k_psp_build(Batch b) {
     const int32_t *pi = b.pidx + (int64_t)t * kPsp;
     const double *Ha = b.Ha + (int64_t)t * b.Na * b.Na, *Hb = b.Hb + (int64_t)t * b.Nb * b.Nb;
     double *H = b.pQ + (int64_t)t * kPsp * kPsp;
-    for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
+    for (int idx = blockIdx.y * 256 + threadIdx.x; idx < n * n; idx += gridDim.y * 256) {
         const int i = idx / n, j = idx % n;
         if (j < i) continue;
         const int64_t I = pi[i], J = pi[j];
@@ -351,220 +351,336 @@ __global__ __launch_bounds__(256) void k_psp_build(Batch b) {
     }
 }
 
-// Householder tridiagonalisation of H_PP in LDS (one block per tuple), Q
-// formed explicitly, and the lowest eigenvector of H_PP (multisection on T's
-// Sturm counts for the lowest eigenvalue, inverse iteration, y = Q z).  Only
-// the lower triangle of the trailing block is kept; the Householder vectors
-// stay below the subdiagonal, as in the usual packed storage.
-__device__ double block_sum256(double v, double *sh) {
-    v = wave_sum(v);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[w] = v;
-    __syncthreads();
-    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+// Factorisation of H_PP = Q T Q^T (T tridiagonal) and the lowest eigenvector
+// y of H_PP, one block per tuple, n <= NP determinants.
+//
+// n^3 operations in a chain of n - 2 reflections: bound by the latency of one
+// workgroup's steps, so the matrix stays in registers, a 4 x 4 patch per
+// thread (all of it, both triangles), and a step is three barriers: the column
+// into LDS, the partial products A v of the waves, their sums.  The norm of
+// the column and the scalar v . A v are formed by every wave for itself.  The
+// reflectors stay in LDS; Q = H_0 ... H_{n-3} is then accumulated backwards,
+// column by column without barriers (16 rows per lane, NP / 16 lanes per
+// column).  NP = 32, 64 and 128 (64, 256 and 1024 threads) keep small P
+// spaces from paying for the large one's barriers.
+// The lowest eigenvalue of T comes from multisection on the leading minors
+// (one point per thread and round), its vector from the twisted factorisation
+// at that eigenvalue (Fernando; Dhillon and Parlett): pivots downwards and
+// upwards by two lanes, joined at the row of the smallest |gamma|.
+// PSPFACTOR_MEASURED
+template <int N> __device__ __forceinline__ double dpp_move(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), N, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), N, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
 }
 
-// number of eigenvalues of the symmetric tridiagonal (d, e) below x
-__device__ int sturm_count(const double *d, const double *e, int n, double x) {
-    int cnt = 0;
-    double q = 1.0;
-    for (int i = 0; i < n; ++i) {
-        q = d[i] - x - (i > 0 ? e[i - 1] * e[i - 1] / q : 0.0);
-        if (q == 0.0) q = -1e-300;
-        cnt += q < 0.0;
-    }
-    return cnt;
-}
+__device__ __forceinline__ double sum_wave(double x) { return add_row32(add_row16(sum_row16(x))); }
 
-__global__ __launch_bounds__(256) void k_psp_factor(Batch b) {
+template <int NP> struct PspFactor {
+    static constexpr int G = NP / 4;          // patches per side
+    static constexpr int NT = G * G;          // threads
+    static constexpr int NW = NT / 64;
+    static constexpr int LPC = NP / 16;       // lanes per column of Q
+    static constexpr size_t lds = sizeof(double) * ((size_t)NP * NP + (size_t)NW * NP + 9 * (size_t)NP + 8);
+};
+
+template <int NP>
+__global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
+    constexpr int G = PspFactor<NP>::G, NT = PspFactor<NP>::NT, NW = PspFactor<NP>::NW, LPC = PspFactor<NP>::LPC;
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = b.psp;
-    constexpr int LD = kPsp + 1;
+    const int r = tid % G, c = tid / G;
     extern __shared__ double lds[];
-    double *A = lds;                 // [n][LD]
-    double *vec = A + kPsp * LD;     // [kPsp] p, then a Householder vector, then z
-    double *sh = vec + kPsp;         // [8]
-    double *cpv = sh + 8;            // [kPsp] Thomas multipliers
-    __shared__ int wcnt[4];
+    double *V = lds;                    // [NP][NP] reflectors
+    double *part = V + NP * NP;         // [NW][NP] the waves' shares of A v
+    double *x = part + NW * NP;         // [2][NP] column
+    double *p = x + 2 * NP;             // [NP] A v
+    double *sd = p + NP, *se = sd + NP; // [NP] T
+    double *pu = se + NP, *pl = pu + NP;   // [NP] pivots downwards and upwards, then e / pivot
+    double *z = pl + NP;                // [NP] eigenvector of T
+    double *sh = z + NP;                // [8]
+    __shared__ int wcnt[NW];
     double *gQ = b.pQ + (int64_t)t * kPsp * kPsp;
     double *dT = b.pT + (int64_t)t * 3 * kPsp, *eT = dT + kPsp, *yv = eT + kPsp;
-    for (int i = wv; i < n; i += 4)
-        for (int j = lane; j <= i; j += 64) A[i * LD + j] = gQ[i * kPsp + j];
+    double a[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            a[i][j] = (4 * r + i < n && 4 * c + j < n) ? gQ[(4 * r + i) * kPsp + 4 * c + j] : 0.0;
+    for (int i = tid; i < NP; i += NT) se[i] = 0.0;
     __syncthreads();
     for (int k = 0; k + 2 < n; ++k) {
-        const int m = n - k - 1;
-        double *B = A + (k + 1) * LD + (k + 1);   // trailing block, B[i * LD + j] for j <= i
-        double *v = A + (k + 1) * LD + k;         // column k below the diagonal, v[i * LD]
-        double part = 0.0;
-        for (int i = tid; i < m; i += 256) part += v[i * LD] * v[i * LD];
-        const double s2 = block_sum256(part, sh);
-        const double x0 = v[0];
-        const double alpha = x0 > 0.0 ? -sqrt(s2) : sqrt(s2);
-        const double v0 = x0 - alpha;
-        const double vn2 = s2 - x0 * x0 + v0 * v0;
+        double *xb = x + (k & 1) * NP;
+        if (c == k >> 2) {
+            const int kj = k & 3;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const double v = kj == 0 ? a[i][0] : (kj == 1 ? a[i][1] : (kj == 2 ? a[i][2] : a[i][3]));
+                xb[4 * r + i] = 4 * r + i > k ? v : 0.0;
+            }
+        }
         __syncthreads();
+        double s2 = 0.0;
+        for (int i = lane; i < NP; i += 64) s2 += xb[i] * xb[i];
+        s2 = sum_wave(s2);
+        const double x0 = xb[k + 1], nx = sqrt(s2), alpha = x0 > 0.0 ? -nx : nx;
+        const double v0 = x0 - alpha, vn2 = 2.0 * fma(-x0, alpha, s2);
         if (!(vn2 > 1e-300)) {   // column already reduced: no reflection
-            if (tid == 0) eT[k] = x0;
-            for (int i = tid; i < m; i += 256) v[i * LD] = 0.0;
-            __syncthreads();
+            if (tid == 0) se[k] = x0;
+            for (int i = tid; i < NP; i += NT) V[k * NP + i] = 0.0;
             continue;
         }
-        if (tid == 0) eT[k] = alpha;
         const double inv = 1.0 / sqrt(vn2);
-        for (int i = tid; i < m; i += 256) v[i * LD] = (i == 0 ? v0 : v[i * LD]) * inv;
-        __syncthreads();
-        // p = B v (B symmetric, lower triangle stored): row i by threads i and
-        // i + 128, one half of the columns each (the same trip count on every
-        // lane), the halves added in a fixed order
-        {
-            const int i = tid & 127, hf = tid >> 7, jh = (m + 1) >> 1;
-            double acc = 0.0;
-            if (i < m) {
-                const int j0 = hf ? jh : 0, j1 = hf ? m : jh;
-#pragma unroll 8
-                for (int j = j0; j < j1; ++j) acc += B[j <= i ? i * LD + j : j * LD + i] * v[j * LD];
-            }
-            if (hf && i < m) cpv[i] = acc;
-            __syncthreads();
-            if (!hf && i < m) vec[i] = acc + cpv[i];
+        auto vel = [&](int i) { return (i == k + 1 ? v0 : xb[i]) * inv; };   // (xb is zero up to row k)
+        double vr[4], vc[4], pr[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            vr[i] = vel(4 * r + i);
+            vc[i] = vel(4 * c + i);
+        }
+        if (tid == 0) se[k] = alpha;
+        if (c == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) V[k * NP + 4 * r + i] = vr[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double q = a[i][0] * vc[0];
+            q = fma(a[i][1], vc[1], q);
+            q = fma(a[i][2], vc[2], q);
+            q = fma(a[i][3], vc[3], q);
+            if (G == 8) q += row_ror<8>(q);
+            if (G <= 16) q = add_row16(q);
+            pr[i] = add_row32(q);
+        }
+        if (lane < G) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[wv * NP + 4 * r + i] = pr[i];
         }
         __syncthreads();
-        part = 0.0;
-        for (int i = tid; i < m; i += 256) part += v[i * LD] * vec[i];
-        const double K = block_sum256(part, sh);
-        // B -= v w^T + w v^T, w = 2 p - 2 K v (lower triangle)
-        for (int i = wv; i < m; i += 4) {
-            const double vi = v[i * LD], wi = 2.0 * vec[i] - 2.0 * K * vi;
-            for (int j = lane; j <= i; j += 64) {
-                const double vj = v[j * LD], wj = 2.0 * vec[j] - 2.0 * K * vj;
-                B[i * LD + j] -= vi * wj + wi * vj;
-            }
+        for (int i = tid; i < NP; i += NT) {
+            double q = 0.0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) q += part[w * NP + i];
+            p[i] = q;
         }
         __syncthreads();
+        double K = 0.0;
+        for (int i = lane; i < NP; i += 64) K += vel(i) * p[i];
+        K = sum_wave(K);
+        double wr[4], wc[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            wr[i] = 2.0 * (p[4 * r + i] - K * vr[i]);
+            wc[i] = 2.0 * (p[4 * c + i] - K * vc[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[i][j] -= vr[i] * wc[j] + wr[i] * vc[j];
     }
-    for (int i = tid; i < n; i += 256) dT[i] = A[i * LD + i];
-    if (tid == 0 && n >= 2) eT[n - 2] = A[(n - 1) * LD + n - 2];
-    if (tid == 0) eT[n - 1] = 0.0;
+    if (r == c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sd[4 * r + i] = a[i][i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (4 * r + i == n - 1 && 4 * c + j == n - 2) se[n - 2] = a[i][j];
     __syncthreads();
-    // Q = H_0 ... H_{n-3}, applied right to left to I and formed in place:
-    // before H_k only rows and columns > k differ from I, and reflector k
-    // lies in column k below the diagonal, outside that block; once H_k is
-    // applied, row and column k become those of I.  The block starts as the
-    // identity on rows and columns >= n - 2.
-    for (int i = tid; i < 4; i += 256) {
-        const int r = n - 2 + (i >> 1), c = n - 2 + (i & 1);
-        if (r >= 0 && c >= 0) A[r * LD + c] = (r == c) ? 1.0 : 0.0;
+    for (int i = tid; i < n; i += NT) {
+        dT[i] = sd[i];
+        eT[i] = se[i];
     }
-    __syncthreads();
-    for (int k = n - 3; k >= 0; --k) {
-        const int m = n - k - 1, rh = (m + 1) >> 1;
-        const double *v = A + (k + 1) * LD + k;   // v[r * LD], r < m
-        // column c of the block by threads c and c + 128 (halves of the rows):
-        // a_c = 2 v . Q[:, c], then Q[:, c] -= a_c v
-        const int ci = tid & 127, hf = tid >> 7, c = k + 1 + ci;
-        const int r0 = hf ? rh : 0, r1 = hf ? m : rh;
-        double acc = 0.0;
-        if (c < n) {
-#pragma unroll 8
-            for (int r = r0; r < r1; ++r) acc += v[r * LD] * A[(k + 1 + r) * LD + c];
-        }
-        if (hf && c < n) cpv[ci] = acc;
-        __syncthreads();
-        if (!hf && c < n) vec[ci] = acc + cpv[ci];
-        __syncthreads();
-        if (c < n) {
-            const double a = 2.0 * vec[ci];
-#pragma unroll 8
-            for (int r = r0; r < r1; ++r) A[(k + 1 + r) * LD + c] -= a * v[r * LD];
-        }
-        __syncthreads();
-        for (int i = tid; i < n - k; i += 256) {
-            A[(k + i) * LD + k] = (i == 0) ? 1.0 : 0.0;
-            A[k * LD + k + i] = (i == 0) ? 1.0 : 0.0;
-        }
-        __syncthreads();
-    }
-    // lowest eigenvalue of T: Gershgorin bounds, then multisection with 256
-    // Sturm counts per round (each round narrows the bracket 257 times)
-    if (tid == 0) {
+    // lowest eigenvalue of T: Gershgorin bounds, then multisection
+    if (tid < 64) {
         double lo = 1e300, hi = -1e300;
-        for (int i = 0; i < n; ++i) {
-            const double r = (i > 0 ? fabs(eT[i - 1]) : 0.0) + (i + 1 < n ? fabs(eT[i]) : 0.0);
-            lo = fmin(lo, dT[i] - r);
-            hi = fmax(hi, dT[i] + r);
+        for (int i = lane; i < n; i += 64) {
+            const double q = (i > 0 ? fabs(se[i - 1]) : 0.0) + fabs(se[i]);
+            lo = fmin(lo, sd[i] - q);
+            hi = fmax(hi, sd[i] + q);
         }
-        sh[4] = lo;
-        sh[5] = hi;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o, 64));
+            hi = fmax(hi, __shfl_xor(hi, o, 64));
+        }
+        if (lane == 0) {
+            sh[0] = lo;
+            sh[1] = hi;
+        }
     }
     __syncthreads();
-    double lo = sh[4], hi = sh[5];
-    const double span = fmax(hi - lo, 1e-300);
-    for (int round = 0; round < 8 && hi - lo > 1e-15 * span; ++round) {
-        const double x = lo + (hi - lo) * ((tid + 1) / 257.0);
-        const bool below = sturm_count(dT, eT, n, x) < 1;   // no eigenvalue below x
-        const uint64_t mk = __ballot(below);
+    // T in units of scale (p: diagonal, x: subdiagonal and its square)
+    const double scale = fmax(sh[1] - sh[0] + fabs(sh[0]), 1e-30);
+    for (int i = tid; i < NP; i += NT) {
+        p[i] = sd[i] / scale;
+        x[i] = se[i] / scale;
+        x[NP + i] = x[i] * x[i];
+    }
+    double lo = sh[0] / scale, hi = sh[1] / scale;
+    __syncthreads();
+    for (int round = 0; round < 10 && hi - lo > 2e-16; ++round) {
+        const double y = lo + (hi - lo) * ((tid + 1) / (double)(NT + 1));
+        // T - y is positive definite iff every leading minor is positive; the
+        // pair of minors is scaled back every eight rows
+        double p0 = 1.0, p1 = p[0] - y;
+        bool pos = p1 > 0.0;
+        for (int i = 1; i < n; ++i) {
+            const double p2 = fma(p[i] - y, p1, -x[NP + i - 1] * p0);
+            p0 = p1;
+            p1 = p2;
+            pos = pos && p2 > 0.0;
+            if ((i & 7) == 0) {
+                const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+                p0 = __builtin_amdgcn_ldexp(p0, ex);
+                p1 = __builtin_amdgcn_ldexp(p1, ex);
+            }
+        }
+        const uint64_t mk = __ballot(pos);
         if (lane == 0) wcnt[wv] = __popcll(mk);
         __syncthreads();
-        const int idx = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];   // first point with an eigenvalue below it
+        int idx = 0;   // points below the lowest eigenvalue
+        for (int w = 0; w < NW; ++w) idx += wcnt[w];
         __syncthreads();
-        const double nlo = idx > 0 ? lo + (hi - lo) * (idx / 257.0) : lo;
-        const double nhi = idx < 256 ? lo + (hi - lo) * ((idx + 1) / 257.0) : hi;
+        const double nlo = idx > 0 ? lo + (hi - lo) * (idx / (double)(NT + 1)) : lo;
+        const double nhi = idx < NT ? lo + (hi - lo) * ((idx + 1) / (double)(NT + 1)) : hi;
         lo = nlo;
         hi = nhi;
     }
-    if (tid == 0) {
-        // T - sigma I positive definite; scale is the size of T's entries
-        // (floored, so that a zero or one-element T still gives finite pivots)
-        const double scale = fmax(span + fabs(lo), 1e-30);
-        const double sigma = lo - 1e-10 * scale;
-        auto clampp = [scale](double p) { return fabs(p) < 1e-14 * scale ? (p >= 0.0 ? 1e-14 : -1e-14) * scale : p; };
-        double *z = vec, *cp = cpv;
-        for (int i = 0; i < n; ++i) z[i] = 1.0;
-        for (int rep = 0; rep < 3; ++rep) {
-            // Thomas on (T - sigma I) z_new = z
-            double piv = clampp(dT[0] - sigma);
-            cp[0] = (n > 1 ? eT[0] : 0.0) / piv;
-            z[0] = z[0] / piv;
-            for (int i = 1; i < n; ++i) {
-                piv = clampp(dT[i] - sigma - eT[i - 1] * cp[i - 1]);
-                cp[i] = (i + 1 < n ? eT[i] : 0.0) / piv;
-                z[i] = (z[i] - eT[i - 1] * z[i - 1]) / piv;
+    // twisted factorisation of T - lo, by the first wave
+    if (tid < 64) {
+        auto keep = [](double q) { return fabs(q) < 1e-18 ? (q >= 0.0 ? 1e-18 : -1e-18) : q; };
+        if (lane < 2) {
+            // lane 0: pu_i = d_i - e_{i-1}^2 / pu_{i-1}; lane 1: pl_i = d_i - e_i^2 / pl_{i+1}
+            const int st = lane ? -1 : 1, i0 = lane ? n - 1 : 0;
+            double *out = lane ? pl : pu;
+            double q = keep(p[i0] - lo);
+            out[i0] = q;
+            for (int s = 1; s < n; ++s) {
+                const int i = i0 + st * s;
+                q = keep(fma(-x[NP + (lane ? i : i - 1)], fast_rcp(q), p[i] - lo));
+                out[i] = q;
             }
-            for (int i = n - 2; i >= 0; --i) z[i] -= cp[i] * z[i + 1];
-            double mz = 0.0;
-            for (int i = 0; i < n; ++i) mz = fmax(mz, fabs(z[i]));
-            double nz = 0.0;
-            for (int i = 0; i < n; ++i) {
-                z[i] /= mz;
-                nz += z[i] * z[i];
-            }
-            nz = 1.0 / sqrt(nz);
-            for (int i = 0; i < n; ++i) z[i] *= nz;
         }
+        wave_sync();
+        double best = 1e300;
+        int kb = 0;
+        for (int i = lane; i < n; i += 64) {
+            const double gam = fabs(pu[i] + pl[i] - (p[i] - lo));
+            if (gam < best) {
+                best = gam;
+                kb = i;
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double q = __shfl_xor(best, o, 64);
+            const int kq = __shfl_xor(kb, o, 64);
+            if (q < best || (q == best && kq < kb)) {
+                best = q;
+                kb = kq;
+            }
+        }
+        wave_sync();
+        for (int i = lane; i < n; i += 64) {   // multipliers towards the ends
+            pu[i] = -x[i] * fast_rcp(pu[i]);
+            pl[i] = i > 0 ? -x[i - 1] * fast_rcp(pl[i]) : 0.0;
+        }
+        wave_sync();
+        if (lane == 0) {
+            double q = 1.0;
+            z[kb] = q;
+            for (int i = kb - 1; i >= 0; --i) z[i] = q = pu[i] * q;
+        } else if (lane == 1) {
+            double q = 1.0;
+            for (int i = kb + 1; i < n; ++i) z[i] = q = pl[i] * q;
+        }
+        wave_sync();
+        double nz = 0.0;
+        for (int i = lane; i < n; i += 64) nz += z[i] * z[i];
+        nz = 1.0 / sqrt(sum_wave(nz));
+        for (int i = lane; i < n; i += 64) z[i] *= nz;
     }
-    __syncthreads();
-    // y = Q z, Q to global
-    for (int i = tid; i < n; i += 256) {
-        double acc = 0.0;
-#pragma unroll 8
-        for (int j = 0; j < n; ++j) acc += A[i * LD + j] * vec[j];
-        yv[i] = acc;
+    // Q, column cq: H_k applied for k = n - 3 .. 0 to the unit vector; lane j
+    // of the column's LPC lanes holds the row pairs 2 (j + LPC m), 2 (j + LPC m) + 1
+    const int cq = tid / LPC, j = tid % LPC;
+    double q0[8], q1[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        q0[m] = 2 * (j + LPC * m) == cq ? 1.0 : 0.0;
+        q1[m] = 2 * (j + LPC * m) + 1 == cq ? 1.0 : 0.0;
+    }
+    // (columns up to k of the product are still unit vectors orthogonal to v_k)
+    const int ctop = ((wv << 6) + 63) / LPC;   // the wave's last column
+    for (int k = n - 3; k >= 0; --k) {
+        if (k >= ctop) continue;
+        const dbl2v *v = reinterpret_cast<const dbl2v *>(V + k * NP) + j;
+        dbl2v vv[8];
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            vv[m] = v[LPC * m];
+            s = fma(vv[m].x, q0[m], s);
+            s = fma(vv[m].y, q1[m], s);
+        }
+        s += dpp_move<0xB1>(s);                    // lane ^ 1
+        if (LPC >= 4) s += dpp_move<0x4E>(s);      // lane ^ 2
+        if (LPC >= 8) s += dpp_move<0x141>(s);     // the other half of eight lanes
+        s *= -2.0;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            q0[m] = fma(s, vv[m].x, q0[m]);
+            q1[m] = fma(s, vv[m].y, q1[m]);
+        }
     }
     double *gQt = b.pQt + (int64_t)t * kPsp * kPsp;
-    for (int i = wv; i < n; i += 4)
-        for (int j = lane; j < n; j += 64) {
-            gQ[i * kPsp + j] = A[i * LD + j];
-            gQt[i * kPsp + j] = A[j * LD + i];
+    if (cq < n) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int i = 2 * (j + LPC * m);
+            if (i < n) {
+                gQ[i * kPsp + cq] = q0[m];
+                gQt[cq * kPsp + i] = q0[m];
+            }
+            if (i + 1 < n) {
+                gQ[(i + 1) * kPsp + cq] = q1[m];
+                gQt[cq * kPsp + i + 1] = q1[m];
+            }
         }
+    }
+    __syncthreads();   // z complete, V no longer read
+    // y = Q z: every column's lanes leave z_c Q[:, c] in V (row i, column c), summed by rows
+    const double zc = cq < n ? z[cq] : 0.0;
+    constexpr int LD = NP + 1;
+    static_assert((size_t)NP * LD <= (size_t)NP * NP + PspFactor<NP>::NW * NP, "y sums");
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const int i = 2 * (j + LPC * m);
+        V[cq * LD + i] = zc * q0[m];
+        V[cq * LD + i + 1] = zc * q1[m];
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += NT) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int q = 0; q < n; ++q) s += V[q * LD + i];
+        yv[i] = s;
+    }
 }
 
-size_t psp_factor_lds() { return sizeof(double) * ((size_t)kPsp * (kPsp + 1) + 2 * kPsp + 8); }
+template <int NP> static void launch_psp_factor(const Batch &b, hipStream_t s) {
+    hipLaunchKernelGGL(k_psp_factor<NP>, dim3(b.B), dim3(PspFactor<NP>::NT), PspFactor<NP>::lds, s, b);
+}
 
 hipError_t launch_pspace(const Batch &b, hipStream_t s) {
     if (b.psp <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_psp_select, dim3(b.B), dim3(256), 0, s, b);
-    hipLaunchKernelGGL(k_psp_build, dim3(b.B), dim3(256), 0, s, b);
-    hipLaunchKernelGGL(k_psp_factor, dim3(b.B), dim3(256), psp_factor_lds(), s, b);
+    hipLaunchKernelGGL(k_psp_build, dim3(b.B, (b.psp * b.psp + 2047) / 2048), dim3(256), 0, s, b);
+    if (b.psp <= 32) launch_psp_factor<32>(b, s);
+    else if (b.psp <= 64) launch_psp_factor<64>(b, s);
+    else launch_psp_factor<128>(b, s);
     return hipGetLastError();
 }
 
@@ -1582,7 +1698,8 @@ hipError_t init_kernels() {
     hipError_t e = init_sigma_kernels();
     if (e != hipSuccess) return e;
     if ((e = init_whole_kernels()) != hipSuccess) return e;
-    return hipFuncSetAttribute((const void *)k_psp_factor, hipFuncAttributeMaxDynamicSharedMemorySize, (int)psp_factor_lds());
+    return hipFuncSetAttribute((const void *)k_psp_factor<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)PspFactor<128>::lds);
 }
 
 }  // namespace mbefci
