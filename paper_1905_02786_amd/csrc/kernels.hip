@@ -14,6 +14,7 @@
 #include "device.h"
 #include "smalleig.h"
 #include "symmetry.h"
+#include "tridiag.h"
 
 namespace mbefci {
 
@@ -367,14 +368,14 @@ __global__ __launch_bounds__(256) void k_psp_build(Batch b) {
 // (one point per thread and round), its vector from the twisted factorisation
 // at that eigenvalue (Fernando; Dhillon and Parlett): pivots downwards and
 // upwards by two lanes, joined at the row of the smallest |gamma|.
-// PSPFACTOR_MEASURED
+// At 128 determinants 337-531 us a launch (up to one tuple per CU; 680 tuples),
+// 74 us at 64, 43-54 us at 32; 1050 us and 190 us with the matrix in LDS and
+// nine barriers a step.
 template <int N> __device__ __forceinline__ double dpp_move(double x) {
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), N, 0xF, 0xF, true);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), N, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
-
-__device__ __forceinline__ double sum_wave(double x) { return add_row32(add_row16(sum_row16(x))); }
 
 template <int NP> struct PspFactor {
     static constexpr int G = NP / 4;          // patches per side
@@ -584,20 +585,39 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
             }
         }
         wave_sync();
-        for (int i = lane; i < n; i += 64) {   // multipliers towards the ends
-            pu[i] = -x[i] * fast_rcp(pu[i]);
+        for (int i = lane; i < n; i += 64) {   // reciprocals, and multipliers towards the ends
+            pu[i] = fast_rcp(pu[i]);
             pl[i] = i > 0 ? -x[i - 1] * fast_rcp(pl[i]) : 0.0;
         }
         wave_sync();
         if (lane == 0) {
             double q = 1.0;
             z[kb] = q;
-            for (int i = kb - 1; i >= 0; --i) z[i] = q = pu[i] * q;
+            for (int i = kb - 1; i >= 0; --i) z[i] = q = -x[i] * pu[i] * q;
         } else if (lane == 1) {
             double q = 1.0;
             for (int i = kb + 1; i < n; ++i) z[i] = q = pl[i] * q;
         }
         wave_sync();
+        // one step of inverse iteration on it: the twisted vector still holds
+        // the other eigenvectors to |lambda - lo| / gap
+        if (lane == 0) {
+            double q = z[0];
+            for (int i = 1; i < n; ++i) z[i] = q = fma(-x[i - 1] * pu[i - 1], q, z[i]);
+            z[n - 1] = q = z[n - 1] * pu[n - 1];
+            for (int i = n - 2; i >= 0; --i) z[i] = q = fma(-x[i], q, z[i]) * pu[i];
+        }
+        wave_sync();
+        double big = 0.0;
+        for (int i = lane; i < n; i += 64) big = fmax(big, fabs(z[i]));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+        // the sign is fixed (positive sum in T's basis): the admixture of the
+        // guess has one of its own
+        double zs = 0.0;
+        for (int i = lane; i < n; i += 64) zs += z[i] / big;
+        const double sb = sum_wave(zs) < 0.0 ? -1.0 / big : 1.0 / big;
+        for (int i = lane; i < n; i += 64) z[i] *= sb;
         double nz = 0.0;
         for (int i = lane; i < n; i += 64) nz += z[i] * z[i];
         nz = 1.0 / sqrt(sum_wave(nz));
@@ -705,108 +725,6 @@ __global__ __launch_bounds__(kPsp) void k_psp_guess(Batch b) {
         double *px = parts(b, t, b.nblk);
         px[0] = sh[0] + (kPsp > 64 ? sh[1] : 0.0);
     }
-}
-
-// After k_ritz: T on the P determinants <- (theta - H_PP)^-1 r_P, solved as
-// Q (theta - T)^-1 Q^T r_P (Thomas, pivots kept away from zero like the
-// diagonal preconditioner); the changes of |T|^2, of the projections V_i . T
-// (on restart the kept vectors' x . T and x2 . T) and of the dots S_i . T
-// (Ax . T, A x2 . T) go to the extra partial block.  T is the vector k_ritz
-// wrote, V_m (V_restart on restart).
-template <int MS>
-__global__ __launch_bounds__(kPsp) void k_psp_fix(Batch b) {
-    const int t = blockIdx.x, i = threadIdx.x, n = b.psp;
-    if (b.status[t] != ST_RUNNING) return;
-    const int m = b.m[t], rs = b.restart[t];
-    const double th = b.theta[t];
-    const double *yy = b.y + (int64_t)t * kMaxSpace;
-    const double *V = b.V + (int64_t)t * b.max_space * b.dim;
-    const double *S = b.S + (int64_t)t * b.max_space * b.dim;
-    double *T = b.V + ((int64_t)t * b.max_space + (rs ? rs : m)) * b.dim;
-    const double *Q = b.pQ + (int64_t)t * kPsp * kPsp, *Qt = b.pQt + (int64_t)t * kPsp * kPsp;
-    const double *dT = b.pT + (int64_t)t * 3 * kPsp, *eT = dT + kPsp;
-    constexpr bool SD = MS <= kSdMax;
-    constexpr int NACC = SD ? kSdOff + MS : 2 + MS;
-    __shared__ double r[kPsp], w[kPsp], cp[kPsp], red[2][NACC];
-    int64_t d = 0;
-    double x = 0.0, ax = 0.0, x2 = 0.0, a2 = 0.0, told = 0.0;
-    if (i < n) {
-        d = b.pidx[(int64_t)t * kPsp + i];
-        if (rs) {
-            x = V[d];
-            ax = S[d];
-            if (rs == 2) {
-                x2 = V[b.dim + d];
-                a2 = S[b.dim + d];
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < MS; ++k)
-                if (k < m) {
-                    x += yy[k] * V[(int64_t)k * b.dim + d];
-                    ax += yy[k] * S[(int64_t)k * b.dim + d];
-                }
-        }
-        r[i] = ax - th * x;
-        told = T[d];
-    }
-    __syncthreads();
-    if (i < n) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = 0; k < n; ++k) s += Q[k * kPsp + i] * r[k];
-        w[i] = s;
-    }
-    __syncthreads();
-    if (i == 0) {
-        auto clampp = [](double p) { return fabs(p) < 1e-8 ? (p >= 0.0 ? 1e-8 : -1e-8) : p; };
-        double piv = clampp(th - dT[0]);
-        cp[0] = (n > 1 ? -eT[0] : 0.0) / piv;
-        w[0] = w[0] / piv;
-        for (int k = 1; k < n; ++k) {
-            piv = clampp(th - dT[k] + eT[k - 1] * cp[k - 1]);
-            cp[k] = (k + 1 < n ? -eT[k] : 0.0) / piv;
-            w[k] = (w[k] + eT[k - 1] * w[k - 1]) / piv;
-        }
-        for (int k = n - 2; k >= 0; --k) w[k] -= cp[k] * w[k + 1];
-    }
-    __syncthreads();
-    double acc[NACC];
-#pragma unroll
-    for (int k = 0; k < NACC; ++k) acc[k] = 0.0;
-    if (i < n) {
-        double tv = 0.0;
-#pragma unroll 8
-        for (int k = 0; k < n; ++k) tv += Qt[k * kPsp + i] * w[k];
-        T[d] = tv;
-        const double dt = tv - told;
-        acc[1] = tv * tv - told * told;
-        if (rs) {
-            acc[2] = x * dt;
-            if (SD) acc[kSdOff] = ax * dt;
-            if (rs == 2) {
-                acc[3] = x2 * dt;
-                if (SD) acc[kSdOff + 1] = a2 * dt;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < MS; ++k)
-                if (k < m) {
-                    acc[2 + k] = V[(int64_t)k * b.dim + d] * dt;
-                    if (SD) acc[kSdOff + k] = S[(int64_t)k * b.dim + d] * dt;
-                }
-        }
-    }
-    const int nx = (SD ? kSdOff : 2) + (rs ? rs : m);
-#pragma unroll
-    for (int k = 0; k < NACC; ++k) {
-        if (k < nx) {
-            const double v = wave_sum(acc[k]);
-            if ((i & 63) == 0) red[i >> 6][k] = v;
-        }
-    }
-    __syncthreads();
-    if (i < nx) parts(b, t, b.nblk)[i] = red[0][i] + (kPsp > 64 ? red[1][i] : 0.0);
 }
 
 __device__ __forceinline__ double guess_noise(int64_t d) {
@@ -956,10 +874,10 @@ hipError_t launch_dots(const Batch &b, VecRef y, int nx_extra, hipStream_t s) {
 // b.G holds the projection B = R^T (V^T H V) R on the orthonormal basis Q =
 // V R.  With g_i = V_i . S_m (partial blocks 0 .. nsum-1; with `sd` the
 // entries i < gemm_dot_first from the S-dots of k_ritz instead), c and s of
-// k_coef1 (column m of R is (-R c, 1) s; c = 0 after the explicit passes):
+// k_step (column m of R is (-R c, 1) s; c = 0 after the explicit passes):
 //   B_im = s ((R^T g)_i - (B c)_i),  B_mm = s^2 (c . B c - 2 c . R^T g + g_m).
 // Block 0 also clears the iteration's counters (running tuples, explicit
-// Gram-Schmidt passes), which k_converge and k_coef1 count after it: no
+// Gram-Schmidt passes), which k_step counts after it: no
 // memset node in the iteration's launches.
 template <int MS>
 __global__ __launch_bounds__(64) void k_small_eig(Batch b, int nsum, int sd) {
@@ -1210,94 +1128,231 @@ __global__ __launch_bounds__(256) void k_ritz(Batch b) {
     else ritz_body<MS, V2, false>(b, t, m, rs);
 }
 
-// convergence test, restart bookkeeping, running count
-__global__ void k_converge(Batch b) {
-    const int t = blockIdx.x;
-    if (threadIdx.x != 0 || b.status[t] != ST_RUNNING) return;
-    const double rn = sqrt(sum_parts(b, t, 0));
+// After k_ritz, one block of 512 threads per tuple: the column sums of its
+// partials, the P-space part of the correction, the convergence test, restart
+// bookkeeping and the running count, and what becomes of the correction.
+//
+// P space: T on the P determinants <- (theta - H_PP)^-1 r_P = Q (theta - T)^-1
+// Q^T r_P (tri_solve), with the changes of |T|^2, of the projections V_i . T
+// (on restart the kept vectors' x . T and x2 . T) and of the dots S_i . T
+// (Ax . T, A x2 . T) added to the sums.  T is the vector k_ritz wrote, V_m
+// (V_restart on restart).
+//
+// The correction on the orthonormal basis: c = Q^T T = R^T d with d the
+// projections V_i . T, and the norm outside the subspace, kept = |T|^2 -
+// |c|^2.  When that keeps at least half of |T|^2 (Kahan's criterion for one
+// classical Gram-Schmidt pass; the difference of squares is then accurate to a
+// few ulps) T joins the basis unchanged: V = Q U gains the column (c,
+// sqrt(kept)), so R = U^-1 gains (-R c, 1) / sqrt(kept), and no vector pass is
+// needed.  Otherwise cgs2 is set, coef = R c (T - V R c is T's part outside
+// the subspace) and the explicit passes follow.
+//
+// Every item is latency: 8 waves share the sums over blocks (16 lanes per
+// column) and the two 128 x 128 products (32 rows each), and the tridiagonal
+// solve takes log2 n steps.  Before, in three launches (128 threads, a serial
+// solve, one lane per column sum): 52-63 us on the 24-orbital expansion's
+// batches and up to 200 us at 200 blocks per tuple; now 10-20 us.
+constexpr int kStepThreads = 512;
+
+template <int MS>
+__global__ __launch_bounds__(kStepThreads) void k_step(Batch b) {
+    const int t = blockIdx.x, tid = threadIdx.x;
+    if (b.status[t] != ST_RUNNING) return;
+    const int m0 = b.m[t], rs = b.restart[t], nk = rs ? rs : m0;
     const double th = b.theta[t];
-    b.rnorm[t] = rn;
-    b.tnorm0[t] = sqrt(sum_parts_x(b, t, 1));
+    constexpr bool SD = MS <= kSdMax;
+    constexpr int NACC = SD ? kSdOff + MS : 2 + MS;
+    constexpr int NPART = kStepThreads / kPsp;   // threads per P determinant
+    __shared__ double sum[NACC], px[NACC], r[kPsp], w[kPsp], red[NPART][kPsp], red2[NPART][kPsp];
+    __shared__ double wsum[NPART][2][MS], ssum[NPART][2][MS], nsum[2];
+    __shared__ TriShared tri;
+    // column sums, 16 lanes a column, in a fixed order
+    for (int c = tid >> 4; c < NACC; c += kStepThreads / 16) {
+        const int l = tid & 15, j = c < 2 ? -1 : (SD && c >= kSdOff ? c - kSdOff : c - 2);
+        double x = 0.0;
+        if (j < nk && !(SD && c < kSdOff && c >= 2 + MS))
+            for (int blk = l; blk < b.nblk; blk += 16) x += parts(b, t, blk)[c];
+        x = sum_row16(x);
+        if (l == 0) {
+            sum[c] = x;
+            px[c] = 0.0;
+        }
+    }
+    if (b.psp > 0) {
+        const int n = b.psp, i = tid & (kPsp - 1), part = tid / kPsp;
+        const double *V = b.V + (int64_t)t * b.max_space * b.dim;
+        const double *S = b.S + (int64_t)t * b.max_space * b.dim;
+        const double *Q = b.pQ + (int64_t)t * kPsp * kPsp, *Qt = b.pQt + (int64_t)t * kPsp * kPsp;
+        const double *dT = b.pT + (int64_t)t * 3 * kPsp, *eT = dT + kPsp;
+        const double *yy = b.y + (int64_t)t * kMaxSpace;
+        double *T = b.V + ((int64_t)t * b.max_space + nk) * b.dim;
+        // this thread's vectors k = part + NPART u at determinant i
+        constexpr int NU = (MS + NPART - 1) / NPART;
+        double vv[NU], ss[NU], x = 0.0, ax = 0.0, told = 0.0;
+        int64_t d = 0;
+        if (i < n) {
+            d = b.pidx[(int64_t)t * kPsp + i];
+            if (part == 0) told = T[d];
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int k = part + NPART * u;
+            vv[u] = ss[u] = 0.0;
+            if (i < n && k < nk) {
+                vv[u] = V[(int64_t)k * b.dim + d];
+                ss[u] = S[(int64_t)k * b.dim + d];
+            }
+            const double yk = rs ? (k == 0 ? 1.0 : 0.0) : (k < nk ? yy[k] : 0.0);   // (restart: V_0 = x, S_0 = A x)
+            x += yk * vv[u];
+            ax += yk * ss[u];
+        }
+        red[part][i] = ax - th * x;
+        __syncthreads();
+        if (tid < kPsp) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < NPART; ++q) s += red[q][i];
+            r[i] = s;
+        }
+        __syncthreads();
+        // out_i = sum_k M[k][i] u_k over this part's rows
+        const int k0 = part * n / NPART, k1 = (part + 1) * n / NPART;
+        auto product = [&](const double *M, const double *u) {
+            double s = 0.0;
+            if (i < n) {
+#pragma unroll 16
+                for (int k = k0; k < k1; ++k) s += M[k * kPsp + i] * u[k];
+            }
+            return s;
+        };
+        red2[part][i] = product(Q, r);
+        __syncthreads();
+        double wv = 0.0, di = 0.0, ei = 0.0, ep = 0.0;
+        if (tid < n) {
+#pragma unroll
+            for (int q = 0; q < NPART; ++q) wv += red2[q][i];
+            di = dT[i];
+            ei = eT[i];
+            ep = i > 0 ? eT[i - 1] : 0.0;
+        }
+        const double uv = tri_solve(tri, n, th, di, ei, ep, wv);
+        if (tid < kPsp) w[i] = uv;
+        __syncthreads();
+        red[part][i] = product(Qt, w);
+        __syncthreads();
+        double tv = 0.0;
+#pragma unroll
+        for (int q = 0; q < NPART; ++q) tv += red[q][i];
+        if (part == 0) {
+            r[i] = i < n ? tv - told : 0.0;
+            if (i < n) T[d] = tv;
+            const double s = sum_wave(i < n ? tv * tv - told * told : 0.0);
+            if ((tid & 63) == 0) nsum[tid >> 6] = s;
+        }
+        __syncthreads();
+        const double dt = r[i];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int k = part + NPART * u;
+            if (k >= nk) break;   // the same in every lane of the part
+            const double a = sum_wave(vv[u] * dt);
+            if ((tid & 63) == 0) wsum[part][(tid >> 6) & 1][u] = a;
+            if (SD) {
+                const double c = sum_wave(ss[u] * dt);
+                if ((tid & 63) == 0) ssum[part][(tid >> 6) & 1][u] = c;
+            }
+        }
+        __syncthreads();
+        if (tid < nk) {
+            const int p = tid % NPART, u = tid / NPART;
+            px[2 + tid] = wsum[p][0][u] + wsum[p][1][u];
+            if (SD) px[kSdOff + tid] = ssum[p][0][u] + ssum[p][1][u];
+        }
+        if (tid == 0) px[1] = nsum[0] + nsum[1];
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    // convergence and restart bookkeeping (every lane takes the same decisions)
+    const int lane = tid;
+    const double rn = sqrt(sum[0]), t2 = sum[1] + px[1];
     int st = ST_RUNNING;
     if (!isfinite(rn) || !isfinite(th)) st = ST_NONFINITE;
-    else if (rn < b.r_tol && fabs(th - b.theta_prev[t]) < b.e_tol) st = ST_DONE;
+    // (a P space that is the whole space holds the exact eigenvector: the
+    // correction's equation is singular there, and a small residual is enough)
+    else if (rn < b.r_tol && (b.psp >= b.dim || fabs(th - b.theta_prev[t]) < b.e_tol)) st = ST_DONE;
     const int it = b.iter[t] + 1;
-    b.iter[t] = it;
     if (st == ST_RUNNING && it >= b.max_iter) st = ST_MAXITER;
-    b.theta_prev[t] = th;
-    const int keep = b.restart[t];
-    if (keep) {   // V_0 = x, S_0 = A x (and V_1, S_1 the kept direction) already written
-        b.m[t] = keep;
-        double *G = b.G + (int64_t)t * kMaxSpace * kMaxSpace, *R = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
-        double *y = b.y + (int64_t)t * kMaxSpace, *zp = b.zp + (int64_t)t * kMaxSpace;
-        G[0] = th;
-        R[0] = 1.0;   // x = Q y has unit norm
-        y[0] = 1.0;
-        if (keep == 2) {
-            G[1] = G[kMaxSpace] = 0.0;
-            G[kMaxSpace + 1] = b.mu[t];
-            R[1] = 0.0;
-            R[kMaxSpace + 1] = 1.0;
-            y[1] = 0.0;
-        }
-        for (int i = 0; i < kMaxSpace; ++i) zp[i] = i == 0 ? 1.0 : 0.0;   // x, in the new coordinates
-    }
-    b.status[t] = st;
-    if (st == ST_RUNNING) atomicAdd(b.counter, 1);
-}
-
-// The correction T = V_m on the orthonormal basis: c = Q^T T = R^T d with d
-// the projections V_i . T (partials 2..m+1 of k_ritz), and the norm outside
-// the subspace, kept = |T|^2 - |c|^2.  When that keeps at least half of
-// |T|^2 (Kahan's criterion for one classical Gram-Schmidt pass; the
-// difference of squares is then accurate to a few ulps) T joins the basis
-// unchanged: V = Q U gains the column (c, sqrt(kept)), so R = U^-1 gains
-// (-R c, 1) / sqrt(kept), and no vector pass is needed.  Otherwise cgs2 is set,
-// coef = R c (T - V R c is T's part outside the subspace) and the explicit
-// second pass and k_tnorm decide.  One block of 64 threads (one wave) per
-// tuple; every lane takes the same decision (the butterfly sums are equal in
-// every lane).
-__global__ void k_coef1(Batch b) {
-    const int t = blockIdx.x;
-    if (b.status[t] != ST_RUNNING) return;
-    const int m = b.m[t], i = threadIdx.x;
     double *R = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
-    __shared__ double dv[kMaxSpace], cv[kMaxSpace];
-    if (i < m) {
-        dv[i] = sum_parts_x(b, t, 2 + i);
-        if (b.max_space <= kSdMax) b.sdot[(int64_t)t * kMaxSpace + i] = sum_parts_x(b, t, kSdOff + i);
+    const int m = nk;
+    if (rs) {   // V_0 = x, S_0 = A x (and V_1, S_1 the kept direction) already written
+        double *G = b.G + (int64_t)t * kMaxSpace * kMaxSpace;
+        double *y = b.y + (int64_t)t * kMaxSpace, *zp = b.zp + (int64_t)t * kMaxSpace;
+        if (lane < kMaxSpace) zp[lane] = lane == 0 ? 1.0 : 0.0;   // x, in the new coordinates
+        if (lane == 0) {
+            b.m[t] = rs;
+            G[0] = th;
+            R[0] = 1.0;   // x = Q y has unit norm
+            y[0] = 1.0;
+            if (rs == 2) {
+                G[1] = G[kMaxSpace] = 0.0;
+                G[kMaxSpace + 1] = b.mu[t];
+                R[1] = 0.0;
+                R[kMaxSpace + 1] = 1.0;
+                y[1] = 0.0;
+            }
+        }
     }
-    __syncthreads();
+    // (before theta_prev is replaced: every lane has read it)
+    wave_sync();
+    if (lane == 0) {
+        b.rnorm[t] = rn;
+        b.tnorm0[t] = sqrt(t2);
+        b.iter[t] = it;
+        b.theta_prev[t] = th;
+        b.status[t] = st;
+    }
+    if (st != ST_RUNNING) return;
+    if (lane == 0) atomicAdd(b.counter, 1);
+    // the correction on the basis (R of a restart: the identity)
+    if (lane < m) {
+        r[lane] = sum[2 + lane] + px[2 + lane];
+        if (SD) b.sdot[(int64_t)t * kMaxSpace + lane] = sum[kSdOff + lane] + px[kSdOff + lane];
+    }
+    wave_sync();
     double c = 0.0;
-    if (i < m) {
-        for (int j = 0; j <= i; ++j) c += R[j * kMaxSpace + i] * dv[j];
-        cv[i] = c;
+    if (lane < m) {
+        if (rs) c = r[lane];
+        else
+            for (int j = 0; j <= lane; ++j) c += R[j * kMaxSpace + lane] * r[j];
+        w[lane] = c;
     }
-    const double c2 = wave_sum(c * c);
-    __syncthreads();
+    const double c2 = sum_wave(c * c);
+    wave_sync();
     double a = 0.0;   // (R c)_i
-    if (i < m)
-        for (int j = i; j < m; ++j) a += R[i * kMaxSpace + j] * cv[j];
-    const double t2 = b.tnorm0[t] * b.tnorm0[t];
+    if (lane < m) {
+        if (rs) a = c;
+        else
+            for (int j = lane; j < m; ++j) a += R[lane * kMaxSpace + j] * w[j];
+    }
     const double kept = t2 - c2;
     const int two = !(kept >= 0.5 * t2);
-    if (i == 0) b.cgs2[t] = two;
+    if (lane == 0) b.cgs2[t] = two;
     if (two) {
-        if (i < m) b.coef[(int64_t)t * kMaxSpace + i] = a;
-        if (i == 0) {
+        if (lane < m) b.coef[(int64_t)t * kMaxSpace + lane] = a;
+        if (lane == 0) {
             atomicAdd(b.counter + 1, 1);   // this iteration (the profiled loop launches the passes only then)
             atomicAdd(b.counter + 2, 1);   // the whole batch
         }
         return;
     }
     if (!(kept > 1e-300) || m >= b.max_space) {
-        if (i == 0) b.status[t] = b.rnorm[t] < b.r_tol ? ST_DONE : (m > 1 ? ST_RESTART : ST_STALLED);
+        if (lane == 0) b.status[t] = rn < b.r_tol ? ST_DONE : (m > 1 ? ST_RESTART : ST_STALLED);
         return;
     }
     const double s = 1.0 / sqrt(kept);
-    if (i < m) b.coef[(int64_t)t * kMaxSpace + i] = c;   // for the new column of the projected matrix
-    if (i < m) R[i * kMaxSpace + m] = -a * s;
-    if (i == m) R[m * kMaxSpace + m] = s;
+    if (lane < m) b.coef[(int64_t)t * kMaxSpace + lane] = c;   // for the new column of the projected matrix
+    if (lane < m) R[lane * kMaxSpace + m] = -a * s;
+    if (lane == m) R[m * kMaxSpace + m] = s;
 }
 
 hipError_t launch_iter_head(const Batch &b, int nsum, bool sd, hipStream_t s) {
@@ -1311,12 +1366,8 @@ hipError_t launch_iter_head(const Batch &b, int nsum, bool sd, hipStream_t s) {
         if (v2) hipLaunchKernelGGL((k_ritz<kMaxSpace, true>), dim3(b.nblk, b.B), dim3(256), 0, s, b);
         else hipLaunchKernelGGL((k_ritz<kMaxSpace, false>), dim3(b.nblk, b.B), dim3(256), 0, s, b);
     }
-    if (b.psp > 0) {
-        if (b.max_space <= 12) hipLaunchKernelGGL(k_psp_fix<12>, dim3(b.B), dim3(kPsp), 0, s, b);
-        else hipLaunchKernelGGL(k_psp_fix<kMaxSpace>, dim3(b.B), dim3(kPsp), 0, s, b);
-    }
-    hipLaunchKernelGGL(k_converge, dim3(b.B), dim3(64), 0, s, b);
-    hipLaunchKernelGGL(k_coef1, dim3(b.B), dim3(64), 0, s, b);
+    if (b.max_space <= 12) hipLaunchKernelGGL(k_step<12>, dim3(b.B), dim3(kStepThreads), 0, s, b);
+    else hipLaunchKernelGGL(k_step<kMaxSpace>, dim3(b.B), dim3(kStepThreads), 0, s, b);
     return hipGetLastError();
 }
 

@@ -56,6 +56,9 @@ __device__ __forceinline__ double sum_row16(double x) {
     return x + row_ror<1>(x);
 }
 
+// Sum over the wave, in every lane.
+__device__ __forceinline__ double sum_wave(double x) { return add_row32(add_row16(sum_row16(x))); }
+
 template <int MS> struct SmallEig {
     static constexpr int IW = MS <= 16 ? 16 : 32;   // lanes of a row group: lane i & (IW - 1) owns row i
     static constexpr int NG = 64 / IW;              // row groups, which share the columns

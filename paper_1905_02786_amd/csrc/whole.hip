@@ -20,6 +20,7 @@
 #include "device.h"
 #include "smalleig.h"
 #include "symmetry.h"
+#include "tridiag.h"
 
 namespace mbefci {
 
@@ -34,7 +35,7 @@ struct WholeShared {
     double red[kWholeWaves][kWholeRed];
     double sum[kWholeRed];
     double y[kMaxSpace], yp[kMaxSpace], z[kMaxSpace];
-    double pr[kPsp], pw[kPsp], pc[kPsp];
+    double pr[kPsp], pw[kPsp];
     double pd[kPsp], pe[kPsp];   // diagonal and subdiagonal of the P-space tridiagonal factor
     double pp[kWholeThreads / kPsp][kPsp];   // partial sums of the P-space products
     double theta, mu;
@@ -43,7 +44,7 @@ struct WholeShared {
 
 // LDS set aside for the static part of k_whole
 constexpr size_t kWholeStatic = 55952;
-static_assert(sizeof(WholeShared) + sizeof(SmallEig<kMaxSpace>) <= kWholeStatic, "static LDS of k_whole");
+static_assert(sizeof(WholeShared) + sizeof(SmallEig<kMaxSpace>) + sizeof(TriShared) <= kWholeStatic, "static LDS of k_whole");
 
 // Dynamic LDS: the vector of the current sigma, the pair integrals, the
 // string Hamiltonians (one when both spins have the same electron count) and
@@ -118,6 +119,7 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(Batch b) {
     const bool same = b.Ha == b.Hb;
     __shared__ WholeShared w;
     __shared__ SmallEig<MS> eig;
+    __shared__ TriShared tri;
     extern __shared__ double wlds[];
     double *cL = wlds;                                    // [dim] vector of the current sigma
     double *eri = cL + ((dim + 1) & ~int64_t(1));         // [P][Kpad] (P|Q) / 2
@@ -340,26 +342,12 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(Batch b) {
             }
             __syncthreads();
             psp_product(Q, w.pr, w.pw);
-            if (tid == 0) {
-                // (theta - Tr) u = w: forward elimination, then back substitution
-                // 1 / pivot, the pivot kept at |p| >= 1e-8
-                auto inv = [](double p) { return fast_rcp(fabs(p) < 1e-8 ? (p >= 0.0 ? 1e-8 : -1e-8) : p); };
-                double ip = inv(theta - dT[0]);
-                double cprev = (n > 1 ? -eT[0] : 0.0) * ip, wprev = w.pw[0] * ip;
-                w.pc[0] = cprev;
-                w.pw[0] = wprev;
-                for (int k = 1; k < n; ++k) {
-                    const double e = eT[k - 1];
-                    ip = inv(theta - dT[k] + e * cprev);
-                    cprev = (k + 1 < n ? -eT[k] : 0.0) * ip;
-                    wprev = (w.pw[k] + e * wprev) * ip;
-                    w.pc[k] = cprev;
-                    w.pw[k] = wprev;
-                }
-                for (int k = n - 2; k >= 0; --k) {
-                    wprev = w.pw[k] - w.pc[k] * wprev;
-                    w.pw[k] = wprev;
-                }
+            {
+                const bool own = tid < n;
+                const double u = tri_solve(tri, n, theta, own ? dT[tid] : 0.0, own ? eT[tid] : 0.0,
+                                           own && tid > 0 ? eT[tid - 1] : 0.0, own ? w.pw[tid] : 0.0);
+                __syncthreads();
+                if (own) w.pw[tid] = u;
             }
             __syncthreads();
             psp_product(Qt, w.pw, w.pr);
@@ -368,7 +356,9 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(Batch b) {
         }
         ++iter;
         if (!isfinite(rn) || !isfinite(theta)) status = ST_NONFINITE;
-        else if (rn < b.r_tol && fabs(theta - theta_prev) < b.e_tol) status = ST_DONE;
+        // (a P space that is the whole space holds the exact eigenvector: the
+        // correction's equation is singular there, and a small residual is enough)
+        else if (rn < b.r_tol && (b.psp >= dim || fabs(theta - theta_prev) < b.e_tol)) status = ST_DONE;
         else if (iter >= b.max_iter) status = ST_MAXITER;
         theta_prev = theta;
         if (status != ST_RUNNING) break;
