@@ -85,6 +85,36 @@ __device__ __forceinline__ double spin_ss(const Batch &b, const double *c, int64
     return acc;
 }
 
+// Tuple and part of workgroup L of a sigma launch of nparts workgroups per
+// tuple (false: none left for it).  Workgroups are handed to the 8 XCDs
+// round-robin by linear id.  The running tuples (b.run, counted by k_step;
+// without skip_done every tuple) are taken eight at a time, one per XCD, all
+// parts of a tuple dispatched back to back so that its vector stays in that
+// XCD's L2; the last n mod 8 tuples have their parts spread over all XCDs.
+// The rule lies there because a tuple on one XCD uses 32 of the 256 CUs: with
+// a fixed tuple t on XCD t mod 8, one tuple (a single product, the last ones
+// of a batch to converge) left 7/8 of the chip idle.
+// One product at (10e,12o): k_linked_wr 655 -> 109 us, k_gemm_hx 333 -> 96 us;
+// 61 order-4 tuples of 60 orbitals: 466 -> 341 ms; batches of hundreds of
+// tuples are unchanged until their last iterations.
+__device__ __forceinline__ bool xcd_map(const Batch &b, int skip_done, int64_t L, int nparts, int &t, int &part) {
+    const int n = skip_done ? __builtin_amdgcn_readfirstlane(b.counter[0]) : b.B;
+    const int64_t whole = (int64_t)(n & ~(kXcds - 1)) * nparts;
+    int k;
+    if (L < whole) {
+        const int64_t j = L / kXcds;
+        k = (int)((j / nparts) * kXcds + L % kXcds);
+        part = (int)(j % nparts);
+    } else {
+        const int64_t j = L - whole;
+        k = (n & ~(kXcds - 1)) + (int)(j / nparts);
+        part = (int)(j % nparts);
+    }
+    if (k >= n) return false;
+    t = skip_done ? __builtin_amdgcn_readfirstlane(b.run[k]) : k;
+    return true;
+}
+
 static inline int grid_for(int64_t work, int per_block, int cap) {
     int64_t g = (work + per_block - 1) / per_block;
     if (g < 1) g = 1;

@@ -138,7 +138,8 @@ struct Batch {
     double *pQ;             // [B][kPsp][kPsp] H_PP, then Q
     double *pQt;            // [B][kPsp][kPsp] Q transposed (coalesced reads of Q w)
     double *pT;             // [B][3][kPsp] diagonal, subdiagonal of T, lowest eigenvector of H_PP
-    int32_t *counter;       // [2] running tuples, tuples whose correction needs the explicit passes
+    int32_t *counter;       // [3] running tuples, of them those whose correction needs the explicit passes, all such passes
+    int32_t *run;           // [B] the running tuples, counter[0] of them (out_status until the batch is finalised)
     // RDM pass (backward): Gram partials and sums
     int nblk_r;
     double *rdm_part;       // [B][nblk_r][NP*NP]

@@ -832,7 +832,11 @@ __global__ void k_init_state(Batch b) {
     b.R[(int64_t)t * kMaxSpace * kMaxSpace] = 1.0;   // V_0 is normalised: Q_0 = V_0
     double *zp = b.zp + (int64_t)t * kMaxSpace;
     for (int i = 0; i < kMaxSpace; ++i) zp[i] = i == 0 ? 1.0 : 0.0;
-    if (t == 0) b.counter[2] = 0;   // explicit Gram-Schmidt passes of the batch
+    b.run[t] = t;
+    if (t == 0) {
+        b.counter[0] = b.B;
+        b.counter[2] = 0;   // explicit Gram-Schmidt passes of the batch
+    }
 }
 
 hipError_t launch_init_state(const Batch &b, hipStream_t s) {
@@ -1312,7 +1316,7 @@ __global__ __launch_bounds__(kStepThreads) void k_step(Batch b) {
         b.status[t] = st;
     }
     if (st != ST_RUNNING) return;
-    if (lane == 0) atomicAdd(b.counter, 1);
+    if (lane == 0) b.run[atomicAdd(b.counter, 1)] = t;   // (in any order: sigma takes the tuples from this list)
     // the correction on the basis (R of a restart: the identity)
     if (lane < m) {
         r[lane] = sum[2 + lane] + px[2 + lane];

@@ -603,6 +603,7 @@ bool carve_batch(mbefci_ctx *ctx, const ClassPlan &cp, int B, Carver &cv, Batch 
     b.iter = cv.take<int32_t>(B);
     b.restart = cv.take<int32_t>(B);
     b.out_status = cv.take<int32_t>(B);
+    b.run = b.out_status;
     b.cgs2 = cv.take<int32_t>(B);
     b.counter = cv.take<int32_t>(3);
     b.nblk_r = cp.nblk_r;

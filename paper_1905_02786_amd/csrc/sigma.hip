@@ -207,16 +207,14 @@ constexpr int kGK = 16;
 // With `dots` (Davidson, sigma of V_m into S_m) the block also writes the
 // partial dots V_i . S_m, gemm_dot_first <= i <= m, of its finished tile to
 // partial block (its tile index) of the tuple (the others come from k_ritz).
-// Grid: one block per (tuple, output tile), mapped so that every tile of
-// tuple t runs on XCD t % 8 and the tiles of one tuple are dispatched back to
-// back: the K-chunks they all read stay in that XCD's L2.
+// Grid: one block per (tuple, output tile), mapped by xcd_map: the K-chunks
+// that the tiles of a tuple all read stay in one XCD's L2.
 template <int WM, int WN>
 __global__ __launch_bounds__(256) void k_gemm_hx(Batch b, VecRef cref, VecRef sref, int skip_done, int dots) {
     constexpr int BM = 32 * WM, BN = 32 * WN;
     const int tx = (int)((b.Nb + BN - 1) / BN), ntiles = tx * (int)((b.Na + BM - 1) / BM);
-    const int64_t L = blockIdx.x, j = L / kXcds;
-    const int t = (int)((j / ntiles) * kXcds + L % kXcds), tile = (int)(j % ntiles);
-    if (t >= b.B) return;
+    int t, tile;
+    if (!xcd_map(b, skip_done, blockIdx.x, ntiles, t, tile)) return;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const uint32_t Na = (uint32_t)b.Na, Nb = (uint32_t)b.Nb;
     const double *C = vref(cref, t, b.dim);
@@ -359,7 +357,7 @@ int gemm_blocks(const Batch &b) {
 template <int WM, int WN>
 static void launch_gemm_hx(const Batch &b, VecRef c, VecRef sig, int skip, int dots, hipStream_t s) {
     const int64_t ntiles = ((b.Nb + 32 * WN - 1) / (32 * WN)) * ((b.Na + 32 * WM - 1) / (32 * WM));
-    const dim3 grid((unsigned)(((b.B + kXcds - 1) / kXcds) * kXcds * ntiles));
+    const dim3 grid((unsigned)(b.B * ntiles));
     hipLaunchKernelGGL((k_gemm_hx<WM, WN>), grid, dim3(256), 0, s, b, c, sig, skip, dots);
 }
 

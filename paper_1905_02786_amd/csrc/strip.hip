@@ -73,17 +73,6 @@ bool strip_fits(const ParamLayout &pl, int64_t Na, int, int) {
     return pl.nA >= 1 && pl.nA <= kMaxActive && strip_lds(pl, Na) <= 160 * 1024 && Na < (1 << 24);
 }
 
-// Workgroups are handed to the 8 XCDs round-robin by linear id; map id L to
-// (tuple, strip) so that every strip of tuple t runs on XCD t % 8 and the
-// strips of one tuple are dispatched back to back: its vector stays in that
-// XCD's L2 while they run.
-__device__ __forceinline__ bool xcd_map(int64_t L, int nstrips, int B, int &t, int &strip) {
-    const int64_t xcd = L % kXcds, j = L / kXcds;
-    t = (int)((j / nstrips) * kXcds + xcd);
-    strip = (int)(j % nstrips);
-    return t < B;
-}
-
 // A compile-time flag passed to generic lambdas.
 template <bool B> struct BoolC {
     static constexpr bool value = B;
@@ -164,7 +153,7 @@ __global__ __launch_bounds__(64 * StripShape<NA>::MT) void k_sigma_strip(Batch b
     constexpr uint32_t DB = DR * kStrip * sizeof(double);   // byte stride of the D buffers
     const int nstrips = (int)((b.Nb + kStrip - 1) / kStrip);
     int t, strip_id;
-    if (!xcd_map(blockIdx.x, nstrips, b.B, t, strip_id)) return;
+    if (!xcd_map(b, skip_done, blockIdx.x, nstrips, t, strip_id)) return;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     // the wave index as a scalar: branches on it are taken per wave, so a
@@ -541,7 +530,7 @@ __global__ __launch_bounds__(256) void k_sigma_linked_gat(Batch b, VecRef cref, 
     constexpr uint32_t DB = KP * kStrip * sizeof(double);   // bytes of one string's D
     const int nstrips = (int)((b.Nb + kStrip - 1) / kStrip);
     int t, strip_id;
-    if (!xcd_map(blockIdx.x, nstrips, b.B, t, strip_id)) return;
+    if (!xcd_map(b, skip_done, blockIdx.x, nstrips, t, strip_id)) return;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -746,7 +735,7 @@ __global__ __launch_bounds__(768) void k_sigma_linked_res(Batch b, VecRef cref, 
     constexpr int NDI = (2 * KP * kStrip + 255) / 256;        // D items per thread of a third
     const int nstrips = (int)((b.Nb + kStrip - 1) / kStrip);
     int t, strip_id;
-    if (!xcd_map(blockIdx.x, nstrips, b.B, t, strip_id)) return;
+    if (!xcd_map(b, skip_done, blockIdx.x, nstrips, t, strip_id)) return;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -971,7 +960,7 @@ __global__ __launch_bounds__(512) void k_sigma_linked_dv(Batch b, VecRef cref, V
     constexpr int NDI = (2 * KP * kStrip + 255) / 256;        // D items per thread of a half
     const int nstrips = (int)((b.Nb + kStrip - 1) / kStrip);
     int t, strip_id;
-    if (!xcd_map(blockIdx.x, nstrips, b.B, t, strip_id)) return;
+    if (!xcd_map(b, skip_done, blockIdx.x, nstrips, t, strip_id)) return;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1205,7 +1194,7 @@ __global__ __launch_bounds__(256) void k_linked_wr(Batch b, VecRef cref, int ski
     constexpr uint32_t RLB = RL * sizeof(double);
     const int nstrips = (int)((b.Nb + kStrip - 1) / kStrip);
     int t, sp;
-    if (!xcd_map(blockIdx.x, nstrips * aparts, b.B, t, sp)) return;
+    if (!xcd_map(b, skip_done, blockIdx.x, nstrips * aparts, t, sp)) return;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const int strip_id = sp / aparts, part = sp % aparts;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1436,7 +1425,7 @@ static hipError_t launch_linked_w_na(const Batch &b, VecRef c, VecRef sig, doubl
     // over up to eight workgroups, until there are 2048 (four per slot)
     int aparts = 1;
     while (aparts < 8 && (int64_t)b.B * nstrips * aparts < 2048 && b.Na >= 32 * (aparts + 1)) ++aparts;
-    const dim3 grid((unsigned)(((b.B + kXcds - 1) / kXcds) * kXcds * nstrips * aparts));
+    const dim3 grid((unsigned)(b.B * nstrips * aparts));
     hipLaunchKernelGGL(k_linked_wr<NA>, grid, dim3(256), linked_lds_w(b.pl), s, b, c, skip, aparts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1472,7 +1461,7 @@ int alpha_beta_kernel(const Batch &b) {
 template <int NA>
 static hipError_t launch_linked_na(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s) {
     const int64_t nstrips = (b.Nb + kStrip - 1) / kStrip;
-    const dim3 grid((unsigned)(((b.B + kXcds - 1) / kXcds) * kXcds * nstrips));
+    const dim3 grid((unsigned)(b.B * nstrips));
     if (b.linked_dv)
         hipLaunchKernelGGL(k_sigma_linked_dv<NA>, grid, dim3(512), linked_lds_dv(b.pl, b.Na), s, b, c, sig, shift,
                            skip);
@@ -1488,7 +1477,7 @@ static hipError_t launch_linked_na(const Batch &b, VecRef c, VecRef sig, double 
 template <int NA>
 static hipError_t launch_strip_na(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s) {
     const int64_t nstrips = (b.Nb + kStrip - 1) / kStrip;
-    const dim3 grid((unsigned)(((b.B + kXcds - 1) / kXcds) * kXcds * nstrips));
+    const dim3 grid((unsigned)(b.B * nstrips));
     hipLaunchKernelGGL(k_sigma_strip<NA>, grid, dim3(StripShape<NA>::NTH), strip_lds(b.pl, b.Na), s, b, c, sig,
                        shift, skip);
     return hipGetLastError();
