@@ -272,9 +272,11 @@ constexpr int kMaxOrb = 64;         // orbital limit of the library
 // layouts; tmp: n^4 doubles of scratch)
 hipError_t launch_rotate_integrals(const double *h0, const double *eri0, const double *U, double *h, double *eri,
                                    double *tmp, int n, hipStream_t s);
-// generalised Fock matrix F and Fock matrix f (n x n) from the full-space
-// gamma and Gamma / 2 (g2h); occ: the no orbitals with density
+// Fock matrix f and, with the full-space Gamma / 2 in g2h, the generalised Fock
+// matrix F (n x n each) from the full-space gamma; occ: the no orbitals with density
 hipError_t launch_fock(const double *h, const double *eri, const double *g1, const double *g2h, const int32_t *occ,
                        int no, int n, double *F, double *f, hipStream_t s);
+// closed-shell Hessian in the occupied-virtual rotations (no (n - no) square)
+hipError_t launch_hf_hessian(const double *eri, const double *f, int no, int n, double *H, hipStream_t s);
 
 }  // namespace mbefci

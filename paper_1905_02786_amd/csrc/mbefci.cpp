@@ -2648,8 +2648,8 @@ mbefci_status mbefci_casscf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_i
 // limited-memory BFGS steps (8 pairs, in the frame of the current orbitals)
 // on the diagonal Hessian estimate 4 (f_aa - f_ii) floored at 0.05, at most
 // 0.5 per element, halved until the energy does not rise; once the gradient
-// is below 1e-5, Newton steps on the Hessian from central differences of the
-// gradient (at most six; the quasi-Newton steps converge slowly there).
+// is below 1e-5, Newton steps (at most six; the quasi-Newton steps converge
+// slowly there).
 // Then the Fock matrix diagonalised in the occupied and the virtual block,
 // each ascending, occupied orbitals first; every column signed so that its
 // largest entry is positive; the context's Hamiltonian replaced by the one in
@@ -2668,14 +2668,11 @@ mbefci_status mbefci_hf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter,
     Carver cv{(char *)ws, wsb};
     double *d_eri0 = cv.take<double>(n4), *d_tmp = cv.take<double>(n4), *d_h0 = cv.take<double>(n2);
     double *d_U = cv.take<double>(n2), *d_f = cv.take<double>(n2), *d_g1 = cv.take<double>(n2);
-    int32_t *d_all = cv.take<int32_t>((size_t)n);
+    (void)cv.take<int32_t>((size_t)n);   // (the bound on the workspace that calls are accepted at)
     if (!cv.ok) return ctx->fail(MBEFCI_ENOMEM, "workspace too small for the Hartree-Fock orbitals");
-    std::vector<int32_t> all(n);
-    for (int p = 0; p < n; ++p) all[p] = p;
     const Mat h0 = ctx->h;
-    HIPCHK(hipMemcpyAsync(d_eri0, ctx->eri.data(), 8 * n4, hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync(d_h0, ctx->h.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync(d_all, all.data(), 4 * (size_t)n, hipMemcpyHostToDevice, ctx->stream));
+    HIPCHK(hipMemcpyAsync(d_eri0, ctx->d_eri, 8 * n4, hipMemcpyDeviceToDevice, ctx->stream));
+    HIPCHK(hipMemcpyAsync(d_h0, ctx->d_h, 8 * n2, hipMemcpyDeviceToDevice, ctx->stream));
     // energy and the Fock matrix in the orbitals C (columns; row-major n x n)
     Mat g1(n2), fao(n2);
     auto evaluate = [&](const Mat &C, double &E, Mat &Fm) -> mbefci_status {
@@ -2686,7 +2683,7 @@ mbefci_status mbefci_hf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter,
                 g1[(size_t)p * n + q] = 2.0 * d;
             }
         HIPCHK(hipMemcpyAsync(d_g1, g1.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
-        hipError_t e = launch_fock(d_h0, d_eri0, d_g1, nullptr, d_all, n, n, d_f, d_f, ctx->stream);
+        hipError_t e = launch_fock(d_h0, d_eri0, d_g1, nullptr, nullptr, 0, n, nullptr, d_f, ctx->stream);
         if (e != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
         HIPCHK(hipMemcpyAsync(fao.data(), d_f, 8 * n2, hipMemcpyDeviceToHost, ctx->stream));
         HIPCHK(hipStreamSynchronize(ctx->stream));
@@ -2731,22 +2728,19 @@ mbefci_status mbefci_hf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter,
             }
         return mat_mul(Cx, mat_exp(K, n), n);
     };
-    // Newton step on the Hessian from central differences of the gradient;
-    // ok = false (and nothing changed) when that Hessian is not positive definite
+    // Newton step; ok = false (and nothing changed) when the Hessian is not
+    // positive definite.  The Hessian comes from the integrals in the current
+    // orbitals (one transformation into the context's arrays, which the
+    // canonical ones replace at the end), formed on the device.
     auto newton_step = [&](bool &ok) -> mbefci_status {
-        const double hs = 1e-4;
         std::vector<double> H((size_t)np * np), x(np, 0.0);
-        for (int kk = 0; kk < np; ++kk) {
-            double Ep, Em;
-            Mat Fp, Fmn;
-            x[kk] = hs;
-            if ((rc = evaluate(rotate(C, x), Ep, Fp)) != MBEFCI_OK) return rc;
-            x[kk] = -hs;
-            if ((rc = evaluate(rotate(C, x), Em, Fmn)) != MBEFCI_OK) return rc;
-            x[kk] = 0.0;
-            const std::vector<double> gp = grad(Fp), gm = grad(Fmn);
-            for (int j = 0; j < np; ++j) H[(size_t)j * np + kk] = (gp[j] - gm[j]) / (2.0 * hs);
-        }
+        HIPCHK(hipMemcpyAsync(d_U, C.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
+        HIPCHK(hipMemcpyAsync(d_f, Fm.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
+        hipError_t e = launch_rotate_integrals(d_h0, d_eri0, d_U, ctx->d_h, ctx->d_eri, d_tmp, n, ctx->stream);
+        if (e == hipSuccess) e = launch_hf_hessian(ctx->d_eri, d_f, no, n, d_tmp, ctx->stream);
+        if (e != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
+        HIPCHK(hipMemcpyAsync(H.data(), d_tmp, 8 * H.size(), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
         // symmetrise into the lower triangle, then Cholesky H = L L^T in place
         for (int a = 0; a < np; ++a)
             for (int b = 0; b < a; ++b) H[(size_t)a * np + b] = 0.5 * (H[(size_t)a * np + b] + H[(size_t)b * np + a]);
