@@ -253,7 +253,7 @@ constexpr int kCcMaxActive = 32;        // active orbitals of a tuple (the whole
 constexpr int kCcMaxIter = 300;         // amplitude iterations
 constexpr double kCcTol = 1e-11;        // largest amplitude change at convergence
 constexpr double kCanonTol = 1e-10;     // off-diagonal Fock elements allowed with (T)
-constexpr int kCcCoopActive = 10;       // tuples of at least this many active orbitals: one cooperative launch each
+constexpr int kCcCoopActive = 10;       // larger tuples (past LDS) of at least this many active orbitals: one cooperative launch each
 constexpr int kCcMaxWgs = 256;          // workgroups of such a launch
 int64_t cc_slice_doubles(int o, int v);
 int ccsd_coop_wgs();
@@ -265,6 +265,19 @@ hipError_t launch_ccsd(const double *h, const double *eri, int n, const int32_t 
                        const int32_t *core, const int32_t *ncore, int stride, int nalpha, int nbeta, double e_const,
                        int ntup, double *work, int64_t slice, int triples, int max_iter, double tol, double *out,
                        int32_t *status, hipStream_t s);
+
+// the same for tuples whose arrays fit in LDS (ccs.hip; every tuple of at most
+// 11 active orbitals): LDS of a tuple of nA orbitals with oa, ob occupied,
+// doubles of its DIIS history in the workspace, and the launch (lds: the
+// largest of the launch's tuples)
+constexpr size_t kCcsMaxLds = 158 * 1024;
+size_t ccs_lds_bytes(int nA, int oa, int ob);
+int64_t ccs_history_doubles(int nA, int oa, int ob);
+hipError_t launch_ccsd_lds(const double *h, const double *eri, int n, const int32_t *act, const int32_t *nact,
+                           const int32_t *core, const int32_t *ncore, int stride, int nalpha, int nbeta, double e_const,
+                           int ntup, size_t lds, double *work, int64_t slice, int triples, int max_iter, double tol,
+                           double *out, int32_t *status, hipStream_t s);
+hipError_t init_ccs_kernels();
 
 // CASSCF expansion reference (casscf.hip)
 constexpr int kMaxOrb = 64;         // orbital limit of the library

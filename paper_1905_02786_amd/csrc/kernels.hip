@@ -1753,6 +1753,7 @@ hipError_t init_kernels() {
     hipError_t e = init_sigma_kernels();
     if (e != hipSuccess) return e;
     if ((e = init_whole_kernels()) != hipSuccess) return e;
+    if ((e = init_ccs_kernels()) != hipSuccess) return e;
     return hipFuncSetAttribute((const void *)k_psp_factor<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)PspFactor<128>::lds);
 }

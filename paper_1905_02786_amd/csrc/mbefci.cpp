@@ -1297,37 +1297,73 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
                             double *out) {
     const int n = ctx->norb;
     std::vector<int32_t> act((size_t)nt * n), core((size_t)nt * n), na((size_t)nt), nc((size_t)nt);
-    for (int64_t t = 0; t < nt; ++t) {
+    const int model = std::max(1, (int)ctx->opt.base_model);
+    auto lists = [&](int64_t t, int64_t row) {   // orbital lists of tuple t into row `row`
         std::vector<char> inA(n, 0);
         for (int p : ctx->ref) inA[p] = 1;
         for (int i = 0; i < k; ++i) inA[tuples[t * k + i]] = 1;
         int a = 0, c = 0;
         for (int p = 0; p < n; ++p) {
-            if (inA[p]) act[(size_t)t * n + a++] = p;
-            else if (p < ctx->nbeta) core[(size_t)t * n + c++] = p;
+            if (inA[p]) act[(size_t)row * n + a++] = p;
+            else if (p < ctx->nbeta) core[(size_t)row * n + c++] = p;
         }
-        na[t] = a;
-        nc[t] = c;
+        na[row] = a;
+        nc[row] = c;
+    };
+    // coupled cluster: tuples whose arrays fit in LDS come first, those of
+    // which two share a CU before the others (ord: the input index of a row)
+    std::vector<int64_t> ord((size_t)nt);
+    int64_t nlds[2] = {0, 0};
+    size_t lds_max[2] = {0, 0};
+    int64_t lds_slice = 0;
+    if (model >= 2) {
+        std::vector<int64_t> bin[3];
+        for (int64_t t = 0; t < nt; ++t) {
+            int a = (int)ctx->ref.size() + k, oa = 0, ob = 0;
+            for (int p : ctx->ref) {
+                oa += p < ctx->nalpha;
+                ob += p < ctx->nbeta;
+            }
+            for (int i = 0; i < k; ++i) {
+                oa += tuples[t * k + i] < ctx->nalpha;
+                ob += tuples[t * k + i] < ctx->nbeta;
+            }
+            const size_t lds = a <= kMaxActive ? ccs_lds_bytes(a, oa, ob) : (size_t)-1;
+            const int q = lds <= kCcsMaxLds / 2 ? 0 : (lds <= kCcsMaxLds ? 1 : 2);
+            bin[q].push_back(t);
+            if (q == 2) continue;
+            lds_max[q] = std::max(lds_max[q], lds);
+            lds_slice = std::max(lds_slice, (ccs_history_doubles(a, oa, ob) + 31) / 32 * 32);
+        }
+        size_t r = 0;
+        for (int q = 0; q < 3; ++q)
+            for (int64_t t : bin[q]) ord[r++] = t;
+        nlds[0] = (int64_t)bin[0].size();
+        nlds[1] = (int64_t)bin[1].size();
+    } else {
+        for (int64_t t = 0; t < nt; ++t) ord[t] = t;
     }
-    const int model = std::max(1, (int)ctx->opt.base_model);
+    for (int64_t t = 0; t < nt; ++t) lists(ord[t], t);
     Carver cv{(char *)ws, wsb};
     int32_t *d_act = cv.take<int32_t>(act.size()), *d_core = cv.take<int32_t>(core.size());
     int32_t *d_na = cv.take<int32_t>(na.size()), *d_nc = cv.take<int32_t>(nc.size());
     double *d_out = cv.take<double>((size_t)nt);
     if (!cv.ok) return ctx->fail(MBEFCI_ENOMEM, "workspace too small for the base-model energies");
     if (model >= 2) {
-        // coupled cluster: one workspace slice per tuple of a launch.  When a
-        // call holds few tuples (fewer than a quarter of the workgroups one
-        // cooperative launch gets), those of at least kCcCoopActive active
-        // orbitals run one at a time on many workgroups (a cooperative launch,
-        // typically the base energy of the whole space); otherwise every tuple
-        // runs batched, one workgroup each, with slices sized for the largest
+        // Tuples that fit in LDS: one workgroup each.  The larger ones: one
+        // workspace slice per tuple of a launch; when a call holds few of them
+        // (fewer than a quarter of the workgroups one cooperative launch
+        // gets), those of at least kCcCoopActive active orbitals run one at a
+        // time on many workgroups (a cooperative launch, typically the base
+        // energy of the whole space), otherwise every tuple runs batched, one
+        // workgroup each, with slices sized for the largest
         const int coop_wgs = ccsd_coop_wgs();
-        const bool few = nt * 4 < coop_wgs;
+        const int64_t first = nlds[0] + nlds[1];
+        const bool few = (nt - first) * 4 < coop_wgs;
         auto coop = [&](int64_t t) { return few && na[t] >= kCcCoopActive; };
         int omax = 0, vmax = 0;
         int64_t big_slice = 0;
-        for (int64_t t = 0; t < nt; ++t) {
+        for (int64_t t = first; t < nt; ++t) {
             int o = 0;
             for (int i = 0; i < na[t]; ++i) o += (act[(size_t)t * n + i] < ctx->nalpha) + (act[(size_t)t * n + i] < ctx->nbeta);
             if (na[t] > kCcMaxActive)
@@ -1346,7 +1382,7 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
         int32_t *d_st = cv.take<int32_t>((size_t)nt);
         double *d_part = cv.take<double>(2 * (size_t)kCcMaxWgs);
         // (at least one aligned unit: a call may hold only large tuples)
-        const int64_t slice = std::max<int64_t>(32, (cc_slice_doubles(omax, vmax) + 31) / 32 * 32);
+        const int64_t slice = std::max<int64_t>({32, lds_slice, first < nt ? (cc_slice_doubles(omax, vmax) + 31) / 32 * 32 : 0});
         const size_t room = cv.ok && cv.size - cv.off > 256 ? (cv.size - cv.off - 256) / 8 : 0;
         const int64_t per = (int64_t)std::min<size_t>(room / (size_t)slice, 4096);
         if (!cv.ok || per < 1 || (size_t)big_slice > room)
@@ -1359,7 +1395,14 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
         HIPCHK(hipMemcpyAsync(d_nc, nc.data(), 4 * nc.size(), hipMemcpyHostToDevice, ctx->stream));
         for (int64_t t0 = 0; t0 < nt;) {
             hipError_t e;
-            if (coop(t0)) {
+            if (t0 < first) {
+                const int q = t0 < nlds[0] ? 0 : 1;
+                const int cnt = (int)std::min<int64_t>(per, (q == 0 ? nlds[0] : first) - t0);
+                e = launch_ccsd_lds(ctx->d_h, ctx->d_eri, n, d_act + t0 * n, d_na + t0, d_core + t0 * n, d_nc + t0, n,
+                                    ctx->nalpha, ctx->nbeta, ctx->e_const, cnt, lds_max[q], d_work, slice, model == 3,
+                                    kCcMaxIter, kCcTol, d_out + t0, d_st + t0, ctx->stream);
+                t0 += cnt;
+            } else if (coop(t0)) {
                 e = launch_ccsd_coop(ctx->d_h, ctx->d_eri, n, d_act + t0 * n, d_na + t0, d_core + t0 * n, d_nc + t0, n,
                                      ctx->nalpha, ctx->nbeta, ctx->e_const, d_work, big_slice, model == 3, kCcMaxIter,
                                      kCcTol, d_out + t0, d_st + t0, wgs, d_part, ctx->stream);
@@ -1374,10 +1417,15 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
             }
             if (e != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
         }
-        std::vector<int32_t> st((size_t)nt);
-        HIPCHK(hipMemcpyAsync(out, d_out, 8 * (size_t)nt, hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipMemcpyAsync(st.data(), d_st, 4 * (size_t)nt, hipMemcpyDeviceToHost, ctx->stream));
+        std::vector<int32_t> row_st((size_t)nt), st((size_t)nt);
+        std::vector<double> res((size_t)nt);
+        HIPCHK(hipMemcpyAsync(res.data(), d_out, 8 * (size_t)nt, hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipMemcpyAsync(row_st.data(), d_st, 4 * (size_t)nt, hipMemcpyDeviceToHost, ctx->stream));
         HIPCHK(hipStreamSynchronize(ctx->stream));
+        for (int64_t t = 0; t < nt; ++t) {
+            out[ord[t]] = res[t];
+            st[ord[t]] = row_st[t];
+        }
         for (int64_t t = 0; t < nt; ++t) {
             if (st[t] == 1)
                 return ctx->fail(MBEFCI_EINVAL, "coupled-cluster base: an orbital energy difference of the reference "
