@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kCcsThreads, 4) void k_ccsd_lds(CcsArgs A) {
     auto E = [&](int p, int q, int r, int s) { return eri[p * n3 + q * n2 + r * n + s]; };
     __shared__ int sact[kMaxOrb], score[kMaxOrb];
     __shared__ double sh[16];
-    __shared__ double Bm[kCcDiis][kCcDiis], Mm[8][8], coef[kCcDiis];
+    __shared__ double Bm[kCcDiis][kCcDiis], Mm[8][8], xs[8], coef[kCcDiis];
     static_assert(kCcDiis + 1 < 8, "DIIS system");
     __shared__ int bad_sh;
     extern __shared__ double lds[];
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(kCcsThreads, 4) void k_ccsd_lds(CcsArgs A) {
         }
         __syncthreads();
         if (tid < 64) {
-            // (nh + 1) x (nh + 1) system [B -1; -1 0] c = [0; -1] by Gauss-Jordan
+            // (nh + 1) x (nh + 1) system [B -1; -1 0] c = [0; -1] by Gaussian
             // elimination with partial pivoting, one matrix element per lane
             const int m = nh, r = tid >> 3, c = tid & 7;
             double scale = 0.0;
@@ -644,10 +644,21 @@ __global__ __launch_bounds__(kCcsThreads, 4) void k_ccsd_lds(CcsArgs A) {
                 const int from = r == q ? piv : (r == piv ? q : r);   // rows q and piv swapped
                 const double pr = Mm[piv][c], pv = Mm[piv][q], mine = Mm[from][c], lead = Mm[from][q];
                 wave_sync();
-                Mm[r][c] = r == q ? mine : mine - lead / pv * pr;
+                Mm[r][c] = r > q ? mine - lead / pv * pr : mine;
                 wave_sync();
             }
-            if (tid < m) coef[tid] = ok ? Mm[tid][7] / Mm[tid][tid] : (tid == slot ? 1.0 : 0.0);
+            // back substitution (not Gauss-Jordan: with fewer amplitudes than
+            // vectors the system is singular to rounding, and the solution has
+            // to keep to its upper rows, the sum rule among them)
+            if (ok) {
+                for (int i = m; i >= 0; --i) {
+                    double w2 = Mm[i][7];
+                    for (int j = i + 1; j <= m; ++j) w2 -= Mm[i][j] * xs[j];
+                    if (tid == 0) xs[i] = w2 / Mm[i][i];
+                    wave_sync();
+                }
+            }
+            if (tid < m) coef[tid] = ok ? xs[tid] : (tid == slot ? 1.0 : 0.0);
         }
         __syncthreads();
         for (int k = tid; k < S.L; k += NT) {
