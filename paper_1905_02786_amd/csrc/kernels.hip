@@ -844,12 +844,11 @@ hipError_t launch_init_state(const Batch &b, hipStream_t s) {
     return hipGetLastError();
 }
 
-// partial dots V_i . y for i < m[t] + nx_extra (running tuples only; with
-// only2, only those whose correction takes the explicit Gram-Schmidt passes)
+// partial dots V_i . y for i < m[t] + nx_extra (running tuples only)
 template <int MS>
-__global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref, int nx_extra, int only2) {
+__global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref, int nx_extra) {
     const int t = blockIdx.y;
-    if (b.status[t] != ST_RUNNING || (only2 && !b.cgs2[t])) return;
+    if (b.status[t] != ST_RUNNING) return;
     const int nx = b.m[t] + nx_extra;
     const double *V = b.V + (int64_t)t * b.max_space * b.dim;
     const double *y = vref(yref, t, b.dim);
@@ -866,10 +865,12 @@ __global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref, int nx_extra
 }
 
 hipError_t launch_dots(const Batch &b, VecRef y, int nx_extra, hipStream_t s) {
-    if (b.max_space <= 12) hipLaunchKernelGGL(k_dots<12>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra, 0);
-    else hipLaunchKernelGGL(k_dots<kMaxSpace>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra, 0);
+    if (b.max_space <= 12) hipLaunchKernelGGL(k_dots<12>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra);
+    else hipLaunchKernelGGL(k_dots<kMaxSpace>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra);
     return hipGetLastError();
 }
+
+constexpr int kNormPart = kParts - 1;   // partial column of |T|^2 after the explicit passes (k_cgs)
 
 // Start of an iteration, one wave per tuple: the projected matrix gains the
 // column of the vector whose sigma was formed last, and its lowest eigenpair
@@ -896,15 +897,37 @@ __global__ __launch_bounds__(64) void k_small_eig(Batch b, int nsum, int sd) {
     double *Gg = b.G + (int64_t)t * kMaxSpace * kMaxSpace;
     const double *Rg = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
     int m = b.m[t];
-    const int n = st0 == ST_RUNNING ? m + 1 : m;   // columns of the basis
+    bool grow = st0 == ST_RUNNING;   // the basis has a new vector, V_m
+    const bool two = grow && m > 0 && b.cgs2[t];
+    double sn = 0.0;   // after the explicit passes: 1 / |V_m|
+    if (two) {
+        // A correction that lies inside the subspace (its projection kept less
+        // than 1e-8 of its norm) adds nothing: the Ritz pair is converged if
+        // the residual is below r_tol (an invariant subspace, e.g. a
+        // one-determinant space); otherwise the tuple restarts from its Ritz
+        // vector now, or has stalled when the subspace already is that one
+        // vector.
+        double x = 0.0;
+        for (int blk = lane; blk < b.nblk; blk += 64) x += parts(b, t, blk)[kNormPart];
+        const double tn = sqrt(sum_wave(x));
+        if (!(tn > 1e-8 * b.tnorm0[t]) || !(tn > 1e-300) || m >= b.max_space) {
+            if (b.rnorm[t] < b.r_tol || m <= 1) {
+                if (lane == 0) b.status[t] = b.rnorm[t] < b.r_tol ? ST_DONE : ST_STALLED;
+                return;
+            }
+            grow = false;
+        }
+        sn = 1.0 / tn;
+    }
+    const int n = grow ? m + 1 : m;   // columns of the basis
     for (int k = lane; k < n * IW; k += 64) {
         const int r = k / IW, c = k & (IW - 1);
         if (c < m && r < m) B[r][c] = Gg[r * kMaxSpace + c];
-        if (c < n && r <= c) R[r][c] = Rg[r * kMaxSpace + c];
+        if (c < n && r <= c) R[r][c] = two && c == m ? (r == m ? sn : 0.0) : Rg[r * kMaxSpace + c];
     }
-    if (st0 == ST_RUNNING) {
+    if (grow) {
         const int i0 = sd ? gemm_dot_first(b, t, m) : 0;
-        const bool two = m > 0 && b.cgs2[t];
+        if (two && lane <= m) b.R[(int64_t)t * kMaxSpace * kMaxSpace + lane * kMaxSpace + m] = lane == m ? sn : 0.0;
         if (lane < i0) gv[lane] = b.sdot[(int64_t)t * kMaxSpace + lane];
         for (int c = i0; c <= m; ++c) {
             double x = 0.0;
@@ -929,7 +952,7 @@ __global__ __launch_bounds__(64) void k_small_eig(Batch b, int nsum, int sd) {
         }
         ++m;
         if (lane == 0) b.m[t] = m;
-    } else if (lane == 0) {
+    } else if (st0 == ST_RESTART && lane == 0) {
         b.status[t] = ST_RUNNING;
     }
     wave_sync();
@@ -954,7 +977,7 @@ __global__ __launch_bounds__(64) void k_small_eig(Batch b, int nsum, int sd) {
     // leaves a norm above 1e-6.  Its coefficients on the stored basis are R w,
     // its Rayleigh quotient w . B w.  The two are orthonormal and the projected
     // matrix on them is diag(theta, mu).
-    const bool rs = m >= b.max_space || st0 == ST_RESTART;
+    const bool rs = m >= b.max_space || !grow;
     double *zp = b.zp + (int64_t)t * kMaxSpace;
     const double zl = lane < m ? z : 0.0;
     int keep = rs ? 1 : 0;
@@ -1375,72 +1398,93 @@ hipError_t launch_iter_head(const Batch &b, int nsum, bool sd, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Coefficients of the second pass on the stored basis, coef = R R^T d with
-// d_i = V_i . T the sums of partials i.  One block of 64 threads per tuple.
-__global__ void k_coef(Batch b) {
-    const int t = blockIdx.x;
-    if (b.status[t] != ST_RUNNING || !b.cgs2[t]) return;
-    const int m = b.m[t], i = threadIdx.x;
-    const double *R = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
-    __shared__ double dv[kMaxSpace], cv[kMaxSpace];
-    if (i < m) dv[i] = sum_parts(b, t, i);
-    __syncthreads();
-    if (i < m) {
-        double c = 0.0;
-        for (int j = 0; j <= i; ++j) c += R[j * kMaxSpace + i] * dv[j];
-        cv[i] = c;
-    }
-    __syncthreads();
-    if (i < m) {
-        double a = 0.0;
-        for (int j = i; j < m; ++j) a += R[i * kMaxSpace + j] * cv[j];
-        b.coef[(int64_t)t * kMaxSpace + i] = a;
-    }
-}
-
-// T -= sum_i coef_i V_i in place (T = V_m; tuples whose correction needs the
-// explicit passes only), and on the second pass the partial |T|^2
-template <int MS, bool V2>
-__global__ __launch_bounds__(256) void k_axpy(Batch b, int second) {
+// Tuples whose correction T = V_m lies too close to the subspace: two passes
+// of classical Gram-Schmidt of T against V_0 .. V_{m-1} (coefficients on the
+// stored basis), each one pass over the basis vectors.  Every other tuple
+// returns at once.  The first pass (coefficients from k_step) also forms the
+// projections of the result, the second sums them (every workgroup for
+// itself, coef = R R^T d) and forms |T|^2; V_m is left unnormalised and
+// 1 / |T| goes into R (k_small_eig, which also decides whether T adds
+// anything).  Two launches an iteration instead of six, five of them empty for
+// most tuples: CGS_MEASURED.
+template <int MS, bool V2, bool SECOND>
+__global__ __launch_bounds__(256) void k_cgs(Batch b) {
     const int t = blockIdx.y;
     if (b.status[t] != ST_RUNNING || !b.cgs2[t]) return;
-    const int m = b.m[t];
+    const int m = b.m[t], tid = threadIdx.x;
     double cf[MS];
-    const double *cp = b.coef + (int64_t)t * kMaxSpace;
+    if (SECOND) {
+        __shared__ double d[MS], c[MS], a[MS];
+        const double *R = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
+        for (int i = tid >> 4; i < MS; i += 16) {
+            double x = 0.0;
+            if (i < m)
+                for (int blk = tid & 15; blk < b.nblk; blk += 16) x += parts(b, t, blk)[i];
+            x = sum_row16(x);
+            if ((tid & 15) == 0) d[i] = x;
+        }
+        __syncthreads();
+        if (tid < m) {
+            double x = 0.0;
+            for (int j = 0; j <= tid; ++j) x += R[j * kMaxSpace + tid] * d[j];
+            c[tid] = x;
+        }
+        __syncthreads();
+        if (tid < MS) {
+            double x = 0.0;
+            if (tid < m)
+                for (int j = tid; j < m; ++j) x += R[tid * kMaxSpace + j] * c[j];
+            a[tid] = x;
+        }
+        __syncthreads();
 #pragma unroll
-    for (int i = 0; i < MS; ++i) cf[i] = (i < m) ? cp[i] : 0.0;
+        for (int i = 0; i < MS; ++i) cf[i] = a[i];
+    } else {
+        const double *cp = b.coef + (int64_t)t * kMaxSpace;
+#pragma unroll
+        for (int i = 0; i < MS; ++i) cf[i] = (i < m) ? cp[i] : 0.0;
+    }
     const double *V = b.V + (int64_t)t * b.max_space * b.dim;
     double *T = b.V + ((int64_t)t * b.max_space + m) * b.dim;
-    double acc[1];
-    acc[0] = 0.0;
+    constexpr int NACC = SECOND ? 1 : MS;
+    double acc[NACC];
+#pragma unroll
+    for (int i = 0; i < NACC; ++i) acc[i] = 0.0;
     // V_i, i < m, through a buffer resource that ends after vector m - 1 (the
     // loads past it read zero, and cf[i] = 0 there): all loads at once
     const __amdgpu_buffer_rsrc_t rV = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<double *>(V), (short)0, (int)((int64_t)m * b.dim * (int64_t)sizeof(double)), 0x00020000);
     const uint32_t vstride = (uint32_t)b.dim * (uint32_t)sizeof(double);
     if (V2) {
-        // pairs of determinants with 16-byte loads (dim even), all loads first
-        typedef double dbl2 __attribute__((ext_vector_type(2)));
+        // pairs of determinants with 16-byte loads (dim even)
         const int64_t n2 = b.dim >> 1;
-        for (int64_t d2 = (int64_t)blockIdx.x * 256 + threadIdx.x; d2 < n2; d2 += (int64_t)gridDim.x * 256) {
+        for (int64_t d2 = (int64_t)blockIdx.x * 256 + tid; d2 < n2; d2 += (int64_t)gridDim.x * 256) {
             const int64_t d = d2 << 1;
             const uint32_t vo = (uint32_t)d * (uint32_t)sizeof(double);
-            dbl2 vv[MS];
+            dbl2v vv[MS];
 #pragma unroll
             for (int i = 0; i < MS; ++i)
-                vv[i] = __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(rV, vo, (uint32_t)i * vstride, 0));
-            dbl2 v = *reinterpret_cast<const dbl2 *>(T + d);
+                vv[i] = __builtin_bit_cast(dbl2v, __builtin_amdgcn_raw_buffer_load_b128(rV, vo, (uint32_t)i * vstride, 0));
+            dbl2v v = *reinterpret_cast<const dbl2v *>(T + d);
 #pragma unroll
             for (int i = 0; i < MS; ++i) {
                 v.x -= cf[i] * vv[i].x;
                 v.y -= cf[i] * vv[i].y;
             }
-            *reinterpret_cast<dbl2 *>(T + d) = v;
-            acc[0] += v.x * v.x;
-            acc[0] += v.y * v.y;
+            *reinterpret_cast<dbl2v *>(T + d) = v;
+            if (SECOND) {
+                acc[0] += v.x * v.x;
+                acc[0] += v.y * v.y;
+            } else {
+#pragma unroll
+                for (int i = 0; i < NACC; ++i) {
+                    acc[i] += vv[i].x * v.x;
+                    acc[i] += vv[i].y * v.y;
+                }
+            }
         }
     } else {
-        for (int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x; d < b.dim; d += (int64_t)gridDim.x * 256) {
+        for (int64_t d = (int64_t)blockIdx.x * 256 + tid; d < b.dim; d += (int64_t)gridDim.x * 256) {
             const uint32_t vo = (uint32_t)d * (uint32_t)sizeof(double);
             double vd[MS];
 #pragma unroll
@@ -1450,77 +1494,40 @@ __global__ __launch_bounds__(256) void k_axpy(Batch b, int second) {
 #pragma unroll
             for (int i = 0; i < MS; ++i) v -= cf[i] * vd[i];
             T[d] = v;
-            acc[0] += v * v;
+            if (SECOND) {
+                acc[0] += v * v;
+            } else {
+#pragma unroll
+                for (int i = 0; i < NACC; ++i) acc[i] += vd[i] * v;
+            }
         }
     }
-    if (second) store_block_partials<1>(b, t, acc, 1);   // |T|^2 after the second pass, for k_tnorm
-}
-
-// 1/|T| into coef[0] and the column of R for V_m = T/|T| (orthogonal to the
-// subspace: R gains the unit column).  A correction that lies inside the subspace (its
-// projection kept less than 1e-8 of its norm) adds nothing: the Ritz pair is
-// converged if the residual is below r_tol (an invariant subspace, e.g. a
-// one-determinant space); otherwise the tuple skips this expansion and
-// restarts from its Ritz vector at the next iteration, or has stalled when the
-// subspace already is that one vector.
-__global__ void k_tnorm(Batch b) {
-    const int t = blockIdx.x;
-    if (threadIdx.x != 0 || b.status[t] != ST_RUNNING || !b.cgs2[t]) return;
-    const double tn = sqrt(sum_parts(b, t, 0));
-    if (!(tn > 1e-8 * b.tnorm0[t]) || !(tn > 1e-300) || b.m[t] >= b.max_space) {
-        b.status[t] = b.rnorm[t] < b.r_tol ? ST_DONE : (b.m[t] > 1 ? ST_RESTART : ST_STALLED);
+    if (!SECOND) {
+        store_block_partials<NACC>(b, t, acc, m);
         return;
     }
-    b.coef[(int64_t)t * kMaxSpace] = 1.0 / tn;
-    const int m = b.m[t];
-    double *R = b.R + (int64_t)t * kMaxSpace * kMaxSpace;
-    for (int i = 0; i < m; ++i) R[i * kMaxSpace + m] = 0.0;
-    R[m * kMaxSpace + m] = 1.0;
+    __shared__ double sh[4];
+    const double x = sum_wave(acc[0]);
+    if ((tid & 63) == 0) sh[tid >> 6] = x;
+    __syncthreads();
+    if (tid == 0) parts(b, t, blockIdx.x)[kNormPart] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// V_m <- V_m / |V_m| in place (tuples that took the second pass)
-__global__ __launch_bounds__(256) void k_store_t(Batch b) {
-    const int t = blockIdx.y;
-    if (b.status[t] != ST_RUNNING || !b.cgs2[t]) return;
-    const double s = b.coef[(int64_t)t * kMaxSpace];
-    double *vm = b.V + ((int64_t)t * b.max_space + b.m[t]) * b.dim;
-    const double *T = vm;
-    if ((b.dim & 1) == 0) {   // 16-byte pairs (every vector 16-byte aligned)
-        typedef double dbl2 __attribute__((ext_vector_type(2)));
-        for (int64_t d2 = (int64_t)blockIdx.x * 256 + threadIdx.x; d2 < (b.dim >> 1); d2 += (int64_t)gridDim.x * 256) {
-            const dbl2 v = *reinterpret_cast<const dbl2 *>(T + 2 * d2);
-            *reinterpret_cast<dbl2 *>(vm + 2 * d2) = dbl2{v.x * s, v.y * s};
-        }
-    } else {
-        for (int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x; d < b.dim; d += (int64_t)gridDim.x * 256)
-            vm[d] = T[d] * s;
-    }
-}
-
-// Tuples whose correction T = V_m lies too close to the subspace: two passes
-// of classical Gram-Schmidt of T against V_0..V_{m-1} (coefficients on the
-// stored basis), then V_m = T/|T|.  Every other tuple returns at once.
-hipError_t launch_orthonormalize(const Batch &b, hipStream_t s) {
+template <int MS, bool V2> static void launch_cgs(const Batch &b, hipStream_t s) {
     const dim3 grid(b.nblk, b.B);
-    VecRef tr{b.V, (int64_t)b.max_space * b.dim, b.m, 0};
-    // first pass: projections from k_ritz, coefficients from k_coef1
-    const bool small = b.max_space <= 12, v2 = (b.dim & 1) == 0;
-    auto axpy = [&](int second) {
-        if (small) {
-            if (v2) hipLaunchKernelGGL((k_axpy<12, true>), grid, dim3(256), 0, s, b, second);
-            else hipLaunchKernelGGL((k_axpy<12, false>), grid, dim3(256), 0, s, b, second);
-        } else {
-            if (v2) hipLaunchKernelGGL((k_axpy<kMaxSpace, true>), grid, dim3(256), 0, s, b, second);
-            else hipLaunchKernelGGL((k_axpy<kMaxSpace, false>), grid, dim3(256), 0, s, b, second);
-        }
-    };
-    axpy(0);
-    if (small) hipLaunchKernelGGL(k_dots<12>, grid, dim3(256), 0, s, b, tr, 0, 1);
-    else hipLaunchKernelGGL(k_dots<kMaxSpace>, grid, dim3(256), 0, s, b, tr, 0, 1);
-    hipLaunchKernelGGL(k_coef, dim3(b.B), dim3(64), 0, s, b);
-    axpy(1);
-    hipLaunchKernelGGL(k_tnorm, dim3(b.B), dim3(64), 0, s, b);
-    hipLaunchKernelGGL(k_store_t, grid, dim3(256), 0, s, b);
+    hipLaunchKernelGGL((k_cgs<MS, V2, false>), grid, dim3(256), 0, s, b);
+    hipLaunchKernelGGL((k_cgs<MS, V2, true>), grid, dim3(256), 0, s, b);
+}
+
+hipError_t launch_orthonormalize(const Batch &b, hipStream_t s) {
+    const bool v2 = (b.dim & 1) == 0;
+    if (b.max_space <= 12) {
+        if (v2) launch_cgs<12, true>(b, s);
+        else launch_cgs<12, false>(b, s);
+    } else {
+        if (v2) launch_cgs<kMaxSpace, true>(b, s);
+        else launch_cgs<kMaxSpace, false>(b, s);
+    }
     return hipGetLastError();
 }
 
