@@ -78,6 +78,8 @@ struct Batch {
     int norb;
     double e_const;
     const double *h, *eri;  // resident integrals (n^2, n^4)
+    char *tab;              // the uploaded block (tables and orbital lists below), tab_bytes of it
+    size_t tab_bytes;
     const uint32_t *strA, *strB, *linkA, *linkB;
     const uint32_t *scatA, *pairB;   // column-strip sigma: alpha scatter table, beta pair links
     // linked-row strip sigma (null la: the all-pairs strip kernel): per alpha

@@ -782,14 +782,14 @@ __global__ void k_guess_pick(Batch b) {
 // eigenvector follows), partial norm^2
 __global__ __launch_bounds__(256) void k_guess_fill(Batch b) {
     const int t = blockIdx.y;
-    const int64_t imin = (int64_t)b.coef[(int64_t)t * kMaxSpace];
+    const int64_t imin = b.psp <= 0 ? (int64_t)b.coef[(int64_t)t * kMaxSpace] : -1;
     double *v0 = b.V + (int64_t)t * b.max_space * b.dim;
     // a P space that is the whole space gives the exact eigenvector: no admixture
     const double amp = (b.psp > 0 && b.psp >= b.dim) ? 0.0 : 1e-3;
     double acc[kParts];
     acc[0] = 0.0;
     for (int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x; d < b.dim; d += (int64_t)gridDim.x * 256) {
-        const double v = (d == imin && b.psp <= 0 ? 1.0 : 0.0) + amp * guess_noise(d);
+        const double v = (d == imin ? 1.0 : 0.0) + amp * guess_noise(d);
         v0[d] = v;
         acc[0] += v * v;
     }
@@ -809,10 +809,46 @@ __global__ __launch_bounds__(256) void k_scale_v0(Batch b) {
         v0[d] *= s;
 }
 
+// The whole guess with a P space, one workgroup per tuple: admixture, P
+// eigenvector, norm, scaling.  One launch instead of four for spaces that a
+// workgroup passes over in a few steps (each launch costs a small class about
+// 4 us; the passes of kGuessOne determinants take that long).
+constexpr int64_t kGuessOne = 16384;
+
+__global__ __launch_bounds__(1024) void k_guess_one(Batch b) {
+    const int t = blockIdx.x, tid = threadIdx.x;
+    __shared__ double sh[16];
+    double *v0 = b.V + (int64_t)t * b.max_space * b.dim;
+    const double *yv = b.pT + (int64_t)t * 3 * kPsp + 2 * kPsp;
+    const double amp = b.psp >= b.dim ? 0.0 : 1e-3;   // (as in k_guess_fill)
+    double acc = 0.0;
+    for (int64_t d = tid; d < b.dim; d += 1024) {
+        const double v = amp * guess_noise(d);
+        v0[d] = v;
+        acc += v * v;
+    }
+    __syncthreads();
+    if (tid < b.psp) {
+        const int64_t d = b.pidx[(int64_t)t * kPsp + tid];
+        const double o = v0[d], nv = o + yv[tid];
+        v0[d] = nv;
+        acc += nv * nv - o * o;
+    }
+    const double s = 1.0 / sqrt(block_sum(acc, sh));
+    __syncthreads();
+    for (int64_t d = tid; d < b.dim; d += 1024) v0[d] *= s;
+}
+
 hipError_t launch_guess(const Batch &b, hipStream_t s) {
+    if (b.psp > 0 && b.dim <= kGuessOne) {
+        hipLaunchKernelGGL(k_guess_one, dim3(b.B), dim3(1024), 0, s, b);
+        return hipGetLastError();
+    }
     dim3 grid(b.nblk, b.B);
-    hipLaunchKernelGGL(k_guess_min, grid, dim3(256), 0, s, b);
-    hipLaunchKernelGGL(k_guess_pick, dim3(b.B), dim3(64), 0, s, b);
+    if (b.psp <= 0) {   // the determinant of lowest diagonal (with a P space its eigenvector instead)
+        hipLaunchKernelGGL(k_guess_min, grid, dim3(256), 0, s, b);
+        hipLaunchKernelGGL(k_guess_pick, dim3(b.B), dim3(64), 0, s, b);
+    }
     hipLaunchKernelGGL(k_guess_fill, grid, dim3(256), 0, s, b);
     if (b.psp > 0) hipLaunchKernelGGL(k_psp_guess, dim3(b.B), dim3(kPsp), 0, s, b);
     hipLaunchKernelGGL(k_guess_norm, dim3(b.B), dim3(64), 0, s, b);

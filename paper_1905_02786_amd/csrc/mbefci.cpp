@@ -314,6 +314,7 @@ struct mbefci_ctx {
     mbefci_class_stats *sigma_cls = nullptr;   // class of the sigma whose events are pending
     bool sigma_pending = false;   // profile: events of the last sigma not read yet
     std::map<std::pair<int, int>, Tables> tables;
+    std::vector<char> staging;   // host side of the batches' copies
 
     mbefci_status fail(mbefci_status s, const std::string &m) {
         err = m;
@@ -513,38 +514,51 @@ bool carve_batch(mbefci_ctx *ctx, const ClassPlan &cp, int B, Carver &cv, Batch 
     b.e_const = ctx->e_const;
     b.h = ctx->d_h;
     b.eri = ctx->d_eri;
+    // what the host uploads, in one block (one copy per batch): string tables,
+    // the orbitals of the tuples, and last the tables of the forms that may
+    // not be used
+    const size_t tab0 = (cv.off + 255) / 256 * 256;
     b.strA = cv.take<uint32_t>(b.Na);
     b.strB = cv.take<uint32_t>(b.Nb);
     b.linkA = cv.take<uint32_t>((size_t)b.Na * b.nentA);
     b.linkB = cv.take<uint32_t>((size_t)b.Nb * b.nentB);
-    b.scatA = cv.take<uint32_t>((size_t)(b.Na + 1) * (cp.pl.P + 1));
     b.pairB = cv.take<uint32_t>((size_t)b.Nb * cp.pl.P);
+    b.act = cv.take<int32_t>((size_t)B * b.nA + 1);
+    b.core = cv.take<int32_t>((size_t)B * b.nC + 1);
+    if (cp.linked_w) {
+        b.lrow_w = cv.take<uint32_t>((size_t)(b.Na + 1) * kLinkedRowsW);
+        b.linc = cv.take<uint32_t>(cp.ta->linc.size());
+    }
+    size_t tab1 = cv.off;
+    b.lrow = b.lscat = nullptr;
+    b.lperm = nullptr;
     if (cp.linked) {
         b.lrow = cv.take<uint32_t>((size_t)(b.Na + 1) * kLinkedRows);
         b.lscat = cv.take<uint32_t>((size_t)(b.Na + 1) * kLinkedRows);
+        b.lperm = cv.take<int32_t>(cp.ta->lperm.size() + 1);
+        if (!cp.linked_w) tab1 = cv.off;
+    }
+    b.scatA = cv.take<uint32_t>((size_t)(b.Na + 1) * (cp.pl.P + 1));
+    if (!cp.linked) tab1 = cv.off;
+    b.tab = cv.base + tab0;
+    b.tab_bytes = tab1 - tab0;
+    if (cp.linked) {
         b.la_stride = linked_a_stride(cp.pl, b.Na);
         b.la = cv.take<double>((size_t)B * b.la_stride);
-        b.lperm = cv.take<int32_t>(cp.ta->lperm.size() + 1);
         b.lpairs = cp.ta->lpairs;
         b.linked_mode = ctx->opt.linked_rows;
         b.linked_dv = cp.linked_dv ? 1 : 0;
         if (cp.linked_w) {
-            b.lrow_w = cv.take<uint32_t>((size_t)(b.Na + 1) * kLinkedRowsW);
-            b.linc = cv.take<uint32_t>(cp.ta->linc.size());
             b.lw_slots = cp.ta->w_slots;
             b.lw_ninc = cp.ta->w_slots;
             b.lw_stride = (int64_t)b.dim * cp.ta->w_slots;
             b.lw = cv.take<double>((size_t)B * b.lw_stride);
         }
     } else {
-        b.lrow = b.lscat = nullptr;
         b.la = nullptr;
         b.la_stride = 0;
-        b.lperm = nullptr;
         b.lpairs = 0;
     }
-    b.act = cv.take<int32_t>((size_t)B * b.nA + 1);
-    b.core = cv.take<int32_t>((size_t)B * b.nC + 1);
     b.params = cv.take<double>((size_t)B * cp.pl.stride);
     b.max_space = davidson ? ctx->opt.max_space : 0;
     b.restart_keep = ctx->opt.max_space >= 3 ? ctx->opt.restart_keep : 1;
@@ -597,14 +611,15 @@ bool carve_batch(mbefci_ctx *ctx, const ClassPlan &cp, int B, Carver &cv, Batch 
     b.theta_prev = cv.take<double>(B);
     b.rnorm = cv.take<double>(B);
     b.tnorm0 = cv.take<double>(B);
-    b.out_e = cv.take<double>(B);
     b.status = cv.take<int32_t>(B);
     b.m = cv.take<int32_t>(B);
-    b.iter = cv.take<int32_t>(B);
     b.restart = cv.take<int32_t>(B);
+    b.cgs2 = cv.take<int32_t>(B);
+    // what the host reads back, in one block
+    b.out_e = cv.take<double>(B);
     b.out_status = cv.take<int32_t>(B);
     b.run = b.out_status;
-    b.cgs2 = cv.take<int32_t>(B);
+    b.iter = cv.take<int32_t>(B);
     b.counter = cv.take<int32_t>(3);
     b.nblk_r = cp.nblk_r;
     if (cp.rdm) {
@@ -617,48 +632,37 @@ bool carve_batch(mbefci_ctx *ctx, const ClassPlan &cp, int B, Carver &cv, Batch 
     return cv.ok;
 }
 
-mbefci_status upload_tables(mbefci_ctx *ctx, const ClassPlan &cp, const Batch &b) {
-    HIPCHK(hipMemcpyAsync((void *)b.strA, cp.ta->strings.data(), 4 * b.Na, hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync((void *)b.strB, cp.tb->strings.data(), 4 * b.Nb, hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync((void *)b.linkA, cp.ta->links.data(), 4 * (size_t)b.Na * b.nentA, hipMemcpyHostToDevice,
-                          ctx->stream));
-    HIPCHK(hipMemcpyAsync((void *)b.linkB, cp.tb->links.data(), 4 * (size_t)b.Nb * b.nentB, hipMemcpyHostToDevice,
-                          ctx->stream));
-    HIPCHK(hipMemcpyAsync((void *)b.scatA, cp.ta->scat.data(), 4 * (size_t)(b.Na + 1) * (b.pl.P + 1),
-                          hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync((void *)b.pairB, cp.tb->pairs.data(), 4 * (size_t)b.Nb * b.pl.P, hipMemcpyHostToDevice,
-                          ctx->stream));
-    if (b.la) {
-        // the slot tables of the LDS forms (not read by the W-in-HBM form,
-        // whose class may have none)
+// Tables and orbital lists of a batch, assembled on the host and sent in one
+// copy (a dozen small ones cost more than the kernels of a small class).
+mbefci_status upload_batch(mbefci_ctx *ctx, const ClassPlan &cp, const Batch &b,
+                           const std::vector<const TupleShape *> &shapes) {
+    std::vector<char> &buf = ctx->staging;
+    buf.resize(b.tab_bytes);
+    auto put = [&](const void *dst, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(buf.data() + (static_cast<const char *>(dst) - b.tab), src, bytes);
+    };
+    put(b.strA, cp.ta->strings.data(), 4 * b.Na);
+    put(b.strB, cp.tb->strings.data(), 4 * b.Nb);
+    put(b.linkA, cp.ta->links.data(), 4 * (size_t)b.Na * b.nentA);
+    put(b.linkB, cp.tb->links.data(), 4 * (size_t)b.Nb * b.nentB);
+    put(b.pairB, cp.tb->pairs.data(), 4 * (size_t)b.Nb * b.pl.P);
+    for (int t = 0; t < b.B; ++t) {
+        put(b.act + (size_t)t * b.nA, shapes[t]->act.data(), 4 * (size_t)b.nA);
+        put(b.core + (size_t)t * b.nC, shapes[t]->core.data(), 4 * (size_t)b.nC);
+    }
+    if (b.lw) {
+        put(b.lrow_w, cp.ta->lrow_w.data(), 4 * cp.ta->lrow_w.size());
+        put(b.linc, cp.ta->linc.data(), 4 * cp.ta->linc.size());
+    } else if (b.la) {
         const std::vector<uint32_t> &lr = b.linked_dv ? cp.ta->lrow_v : cp.ta->lrow,
                                     &ls = b.linked_dv ? cp.ta->lscat_v : cp.ta->lscat;
-        if (!b.lw) {
-            HIPCHK(hipMemcpyAsync((void *)b.lrow, lr.data(), 4 * (size_t)(b.Na + 1) * kLinkedRows,
-                                  hipMemcpyHostToDevice, ctx->stream));
-            HIPCHK(hipMemcpyAsync((void *)b.lscat, ls.data(), 4 * (size_t)(b.Na + 1) * kLinkedRows,
-                                  hipMemcpyHostToDevice, ctx->stream));
-            HIPCHK(hipMemcpyAsync((void *)b.lperm, cp.ta->lperm.data(), 4 * cp.ta->lperm.size(),
-                                  hipMemcpyHostToDevice, ctx->stream));
-        }
-        if (b.lw) {
-            HIPCHK(hipMemcpyAsync((void *)b.lrow_w, cp.ta->lrow_w.data(), 4 * cp.ta->lrow_w.size(),
-                                  hipMemcpyHostToDevice, ctx->stream));
-            HIPCHK(hipMemcpyAsync((void *)b.linc, cp.ta->linc.data(), 4 * cp.ta->linc.size(), hipMemcpyHostToDevice,
-                                  ctx->stream));
-        }
+        put(b.lrow, lr.data(), 4 * (size_t)(b.Na + 1) * kLinkedRows);
+        put(b.lscat, ls.data(), 4 * (size_t)(b.Na + 1) * kLinkedRows);
+        put(b.lperm, cp.ta->lperm.data(), 4 * cp.ta->lperm.size());
+    } else {
+        put(b.scatA, cp.ta->scat.data(), 4 * (size_t)(b.Na + 1) * (b.pl.P + 1));
     }
-    return MBEFCI_OK;
-}
-
-mbefci_status upload_shapes(mbefci_ctx *ctx, const Batch &b, const std::vector<const TupleShape *> &shapes) {
-    std::vector<int32_t> act((size_t)b.B * b.nA + 1, 0), core((size_t)b.B * b.nC + 1, 0);
-    for (int t = 0; t < b.B; ++t) {
-        std::copy(shapes[t]->act.begin(), shapes[t]->act.end(), act.begin() + (size_t)t * b.nA);
-        std::copy(shapes[t]->core.begin(), shapes[t]->core.end(), core.begin() + (size_t)t * b.nC);
-    }
-    HIPCHK(hipMemcpyAsync((void *)b.act, act.data(), 4 * act.size(), hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync((void *)b.core, core.data(), 4 * core.size(), hipMemcpyHostToDevice, ctx->stream));
+    HIPCHK(hipMemcpyAsync(b.tab, buf.data(), b.tab_bytes, hipMemcpyHostToDevice, ctx->stream));
     return MBEFCI_OK;
 }
 
@@ -853,19 +857,25 @@ mbefci_status davidson_finish(mbefci_ctx *ctx, const Batch &b, double *e_out, in
                 return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
         }
     }
+    // energies, statuses, iterations and counters in one copy
     std::vector<int32_t> dst(b.B), dit(b.B);
-    HIPCHK(hipMemcpyAsync(e_out, b.out_e, 8 * (size_t)b.B, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(dst.data(), b.out_status, 4 * (size_t)b.B, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(dit.data(), b.iter, 4 * (size_t)b.B, hipMemcpyDeviceToHost, s));
+    const char *back = reinterpret_cast<const char *>(b.out_e);
+    std::vector<char> &buf = ctx->staging;
+    buf.resize(reinterpret_cast<const char *>(b.counter + 3) - back);
+    HIPCHK(hipMemcpyAsync(buf.data(), back, buf.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    auto got = [&](const void *p) { return buf.data() + (static_cast<const char *>(p) - back); };
+    std::memcpy(e_out, got(b.out_e), 8 * (size_t)b.B);
+    std::memcpy(dst.data(), got(b.out_status), 4 * (size_t)b.B);
+    std::memcpy(dit.data(), got(b.iter), 4 * (size_t)b.B);
     flush_sigma_time(ctx);
     mbefci_class_stats &cs = class_stats(ctx, b);
     cs.tuples += b.B;
     for (int t = 0; t < b.B; ++t) cs.iterations += dit[t];
     {
-        int32_t gs = 0;
-        HIPCHK(hipMemcpy(&gs, b.counter + 2, sizeof(int32_t), hipMemcpyDeviceToHost));
-        ctx->stats.gs_second_pass += gs;
+        int32_t gs[3];
+        std::memcpy(gs, got(b.counter), sizeof(gs));
+        ctx->stats.gs_second_pass += gs[2];
     }
     if (!prof) {
         // sigma applications: the first, then one per iteration that a tuple
@@ -960,9 +970,8 @@ mbefci_status autotune_class(mbefci_ctx *ctx, const ClassKey &key, int nC, const
             const int kid = alpha_beta_kernel(b) * 1000 + tile;
             if (std::find(seen.begin(), seen.end(), kid) != seen.end()) continue;
             seen.push_back(kid);
-            if ((rc = upload_tables(ctx, cp, b)) != MBEFCI_OK) break;
             std::vector<const TupleShape *> sh(sample.begin(), sample.begin() + B);
-            if ((rc = upload_shapes(ctx, b, sh)) != MBEFCI_OK) break;
+            if ((rc = upload_batch(ctx, cp, b, sh)) != MBEFCI_OK) break;
             hipError_t e = launch_gather(b, s);
             if (e == hipSuccess) e = launch_build_hb(b, s);
             if (e == hipSuccess) e = launch_hdiag(b, b.Hd, b.dim, 0, s);
@@ -1080,10 +1089,9 @@ mbefci_status solve_device(mbefci_ctx *ctx, int order, int64_t ntup, const int16
                 ctx->opt = first_opt;
                 return ctx->fail(MBEFCI_ENOMEM, "workspace carve failed");
             }
-            if ((rc = upload_tables(ctx, cp, b)) != MBEFCI_OK) break;
             std::vector<const TupleShape *> sh(B);
             for (int t = 0; t < B; ++t) sh[t] = &shapes[idx[start + t]];
-            if ((rc = upload_shapes(ctx, b, sh)) != MBEFCI_OK) break;
+            if ((rc = upload_batch(ctx, cp, b, sh)) != MBEFCI_OK) break;
             std::vector<double> e(B), gram, wts;
             std::vector<int32_t> st(B);
             const double tb0 = now_ms();
@@ -2310,9 +2318,8 @@ static mbefci_status single_tuple_batch(mbefci_ctx *ctx, int32_t order, const in
     plan_class(ctx, ts.key, ts.nC, cp, false);
     Carver cv{(char *)ws, wsb};
     if (!carve_batch(ctx, cp, 1, cv, b, false)) return ctx->fail(MBEFCI_ENOMEM, "workspace too small");
-    if ((rc = upload_tables(ctx, cp, b)) != MBEFCI_OK) return rc;
     std::vector<const TupleShape *> sh{&ts};
-    if ((rc = upload_shapes(ctx, b, sh)) != MBEFCI_OK) return rc;
+    if ((rc = upload_batch(ctx, cp, b, sh)) != MBEFCI_OK) return rc;
     hipError_t e = launch_gather(b, ctx->stream);
     if (e != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
     e = launch_build_hb(b, ctx->stream);
