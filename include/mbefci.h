@@ -241,7 +241,8 @@ typedef struct {
     double sigma_ms;            /* HIP-event time of the alpha-beta kernel (the MFMA kernel of kernel 5) */
     double gather_ms;           /* of the gather of kernel 5 */
     double sigma_total_ms;      /* of all sigma kernels (with the string-Hamiltonian GEMMs) */
-    double wall_ms;             /* host wall time of the class's batches */
+    double wall_ms;             /* host wall time of the class's batches, each from its start to its end
+                                   (those of several classes can overlap) */
 } mbefci_class_stats;
 
 /* Library version string. */
