@@ -11,6 +11,8 @@
 //   k_pq = h^eff_pq - 1/2 sum_r (pr|rq),  h^eff_pq = h_pq + sum_c [2(pq|cc) - (pc|cq)],
 //   E_core = E_const + sum_c 2 h_cc + sum_cd [2(cc|dd) - (cd|dc)],
 // over p, q, r, s in A and c in the core C.
+#include <type_traits>
+
 #include "device.h"
 #include "smalleig.h"
 #include "symmetry.h"
@@ -357,20 +359,27 @@ __global__ __launch_bounds__(256) void k_psp_build(Batch b) {
 //
 // n^3 operations in a chain of n - 2 reflections: bound by the latency of one
 // workgroup's steps, so the matrix stays in registers, a 4 x 4 patch per
-// thread (all of it, both triangles), and a step is three barriers: the column
-// into LDS, the partial products A v of the waves, their sums.  The norm of
-// the column and the scalar v . A v are formed by every wave for itself.  The
-// reflectors stay in LDS; Q = H_0 ... H_{n-3} is then accumulated backwards,
+// thread (all of it, both triangles), and a step is three barriers: the
+// column's wave makes the reflector (sums and broadcasts on the vector ALU)
+// and leaves it in LDS, where it stays; the partial products A v of the waves;
+// their sums and v . A v.  Waves whose columns are finished only keep the
+// barriers.  The steps are unrolled by four, so that a column's place in the
+// patches is a constant.  Q = H_0 ... H_{n-3} is then accumulated backwards,
 // column by column without barriers (16 rows per lane, NP / 16 lanes per
-// column).  NP = 32, 64 and 128 (64, 256 and 1024 threads) keep small P
-// spaces from paying for the large one's barriers.
-// The lowest eigenvalue of T comes from multisection on the leading minors
-// (one point per thread and round), its vector from the twisted factorisation
-// at that eigenvalue (Fernando; Dhillon and Parlett): pivots downwards and
-// upwards by two lanes, joined at the row of the smallest |gamma|.
-// At 128 determinants 337-531 us a launch (up to one tuple per CU; 680 tuples),
-// 74 us at 64, 43-54 us at 32; 1050 us and 190 us with the matrix in LDS and
-// nine barriers a step.
+// column), the rows above each reflector left out.  NP = 32, 64 and 128 (64,
+// 256 and 1024 threads) keep small P spaces from paying for the large one's
+// barriers.
+// Meanwhile the first wave finds the lowest eigenvalue of T by multisection on
+// the leading minors (one point per lane and round), its vector from the
+// twisted factorisation at that eigenvalue (Fernando; Dhillon and Parlett):
+// pivots downwards and upwards by two lanes, joined at the row of the smallest
+// |gamma|.
+// At 128 determinants 170-211 us a launch (up to one tuple per CU), 73 us at
+// 64, 38-43 us at 32; 315-406, 103 and 58-68 us with the reflector made by
+// every wave for itself from a column in LDS, a branch per patch element, and
+// the eigenvalue found by all threads before Q; 1050 us and 190 us with the
+// matrix in LDS and nine barriers a step.  Of the 128-determinant launch the
+// reflections take 145 us, Q 24 us.
 template <int N> __device__ __forceinline__ double dpp_move(double x) {
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), N, 0xF, 0xF, true);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), N, 0xF, 0xF, true);
@@ -383,23 +392,24 @@ template <int NP> struct PspFactor {
     static constexpr int NW = NT / 64;
     static constexpr int LPC = NP / 16;       // lanes per column of Q
     static constexpr size_t lds = sizeof(double) * ((size_t)NP * NP + (size_t)NW * NP + 9 * (size_t)NP + 8);
+    static constexpr int CW = 4 * 64 / G;     // columns per wave
 };
 
 template <int NP>
 __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
-    constexpr int G = PspFactor<NP>::G, NT = PspFactor<NP>::NT, NW = PspFactor<NP>::NW, LPC = PspFactor<NP>::LPC;
+    constexpr int G = PspFactor<NP>::G, NT = PspFactor<NP>::NT, NW = PspFactor<NP>::NW, LPC = PspFactor<NP>::LPC,
+                  CW = PspFactor<NP>::CW;
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = b.psp;
     const int r = tid % G, c = tid / G;
-    extern __shared__ double lds[];
+    extern __shared__ __attribute__((aligned(16))) double lds[];
     double *V = lds;                    // [NP][NP] reflectors
     double *part = V + NP * NP;         // [NW][NP] the waves' shares of A v
-    double *x = part + NW * NP;         // [2][NP] column
+    double *x = part + NW * NP;         // [2][NP]
     double *p = x + 2 * NP;             // [NP] A v
     double *sd = p + NP, *se = sd + NP; // [NP] T
     double *pu = se + NP, *pl = pu + NP;   // [NP] pivots downwards and upwards, then e / pivot
     double *z = pl + NP;                // [NP] eigenvector of T
-    double *sh = z + NP;                // [8]
-    __shared__ int wcnt[NW];
+    double *sh = z + NP;                // [2] shares of v . A v
     double *gQ = b.pQ + (int64_t)t * kPsp * kPsp;
     double *dT = b.pT + (int64_t)t * 3 * kPsp, *eT = dT + kPsp, *yv = eT + kPsp;
     double a[4][4];
@@ -409,76 +419,117 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
         for (int j = 0; j < 4; ++j)
             a[i][j] = (4 * r + i < n && 4 * c + j < n) ? gQ[(4 * r + i) * kPsp + 4 * c + j] : 0.0;
     for (int i = tid; i < NP; i += NT) se[i] = 0.0;
+    for (int i = tid; i < NW * NP; i += NT) part[i] = 0.0;
+    if (tid < 2) sh[tid] = 0.0;
     __syncthreads();
-    for (int k = 0; k + 2 < n; ++k) {
-        double *xb = x + (k & 1) * NP;
-        if (c == k >> 2) {
-            const int kj = k & 3;
+    const int wc0 = wv * CW;   // the wave's first column
+    for (int kb = 0; 4 * kb + 2 < n; ++kb) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double v = kj == 0 ? a[i][0] : (kj == 1 ? a[i][1] : (kj == 2 ? a[i][2] : a[i][3]));
-                xb[4 * r + i] = 4 * r + i > k ? v : 0.0;
+        for (int kj = 0; kj < 4; ++kj) {   // (unrolled: the column's place in the patches is a constant)
+            const int k = 4 * kb + kj;
+            if (k + 2 >= n) break;
+            double *vk = V + k * NP;
+            if (wv == k / CW) {   // the column's wave makes the reflector
+                double xi[4], s2 = 0.0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    xi[i] = 4 * r + i > k ? a[i][kj] : 0.0;
+                    s2 = fma(xi[i], xi[i], s2);
+                }
+                if (G == 8) {
+                    s2 += dpp_move<0xB1>(s2);
+                    s2 += dpp_move<0x4E>(s2);
+                    s2 += dpp_move<0x141>(s2);
+                } else {
+                    s2 = sum_row16(s2);
+                    if (G == 32) s2 = add_row16(s2);
+                }
+                const double xs = xi[(kj + 1) & 3];
+                const int l0 = (kb * G & 63) + kb + (kj == 3);   // row k + 1 of the column
+                const double x0 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xs), l0),
+                                                   __builtin_amdgcn_readlane(__double2loint(xs), l0));
+                // a column already reduced has no reflection (v = 0)
+                const bool red = !(s2 > 1e-300);
+                const double nx = s2 * fast_rsq(s2), alpha = x0 > 0.0 ? -nx : nx;
+                const double inv = red ? 0.0 : fast_rsq(2.0 * fma(-x0, alpha, s2));
+                if (c == kb) {
+                    dbl2v *o = reinterpret_cast<dbl2v *>(vk + 4 * r);
+                    double v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = red ? 0.0 : (4 * r + i == k + 1 ? x0 - alpha : xi[i]) * inv;
+                    o[0] = dbl2v{v[0], v[1]};
+                    o[1] = dbl2v{v[2], v[3]};
+                    if (r == 0) se[k] = red ? x0 : alpha;
+                }
+            }
+            __syncthreads();
+            const bool act = wc0 + CW > k + 1;   // (columns up to k are finished)
+            double vr[4], vc[4];
+            if (act) {
+                const dbl2v *qr = reinterpret_cast<const dbl2v *>(vk + 4 * r);
+                const dbl2v *qc = reinterpret_cast<const dbl2v *>(vk + 4 * c);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const dbl2v u = qr[i], w = qc[i];
+                    vr[2 * i] = u.x;
+                    vr[2 * i + 1] = u.y;
+                    vc[2 * i] = w.x;
+                    vc[2 * i + 1] = w.y;
+                }
+                double pr[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    double q = a[i][0] * vc[0];
+                    q = fma(a[i][1], vc[1], q);
+                    q = fma(a[i][2], vc[2], q);
+                    q = fma(a[i][3], vc[3], q);
+                    if (G == 8) q += row_ror<8>(q);
+                    if (G <= 16) q = add_row16(q);
+                    pr[i] = add_row32(q);
+                }
+                if (lane < G) {
+                    dbl2v *o = reinterpret_cast<dbl2v *>(part + wv * NP + 4 * r);
+                    o[0] = dbl2v{pr[0], pr[1]};
+                    o[1] = dbl2v{pr[2], pr[3]};
+                }
+            } else if (wc0 + CW == k + 1 && lane < G) {   // no share any more
+                dbl2v *o = reinterpret_cast<dbl2v *>(part + wv * NP + 4 * r);
+                o[0] = o[1] = dbl2v{0.0, 0.0};
+            }
+            __syncthreads();
+            if (tid < (NP > 64 ? NP : 64)) {
+                double K = 0.0;
+                if (NP >= 64 || tid < NP) {
+                    double q[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) q[w & 3] += part[w * NP + tid];
+                    const double pi = (q[0] + q[1]) + (q[2] + q[3]);
+                    p[tid] = pi;
+                    K = vk[tid] * pi;
+                }
+                K = sum_wave(K);
+                if (lane == 0) sh[wv] = K;
+            }
+            __syncthreads();
+            if (act) {
+                const double K = NP > 64 ? sh[0] + sh[1] : sh[0];
+                const dbl2v *qr = reinterpret_cast<const dbl2v *>(p + 4 * r);
+                const dbl2v *qc = reinterpret_cast<const dbl2v *>(p + 4 * c);
+                double wr[4], wc[4];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const dbl2v u = qr[i], w = qc[i];
+                    wr[2 * i] = 2.0 * fma(-K, vr[2 * i], u.x);
+                    wr[2 * i + 1] = 2.0 * fma(-K, vr[2 * i + 1], u.y);
+                    wc[2 * i] = 2.0 * fma(-K, vc[2 * i], w.x);
+                    wc[2 * i + 1] = 2.0 * fma(-K, vc[2 * i + 1], w.y);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) a[i][j] = fma(-vr[i], wc[j], fma(-wr[i], vc[j], a[i][j]));
             }
         }
-        __syncthreads();
-        double s2 = 0.0;
-        for (int i = lane; i < NP; i += 64) s2 += xb[i] * xb[i];
-        s2 = sum_wave(s2);
-        const double x0 = xb[k + 1], nx = sqrt(s2), alpha = x0 > 0.0 ? -nx : nx;
-        const double v0 = x0 - alpha, vn2 = 2.0 * fma(-x0, alpha, s2);
-        if (!(vn2 > 1e-300)) {   // column already reduced: no reflection
-            if (tid == 0) se[k] = x0;
-            for (int i = tid; i < NP; i += NT) V[k * NP + i] = 0.0;
-            continue;
-        }
-        const double inv = 1.0 / sqrt(vn2);
-        auto vel = [&](int i) { return (i == k + 1 ? v0 : xb[i]) * inv; };   // (xb is zero up to row k)
-        double vr[4], vc[4], pr[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            vr[i] = vel(4 * r + i);
-            vc[i] = vel(4 * c + i);
-        }
-        if (tid == 0) se[k] = alpha;
-        if (c == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) V[k * NP + 4 * r + i] = vr[i];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double q = a[i][0] * vc[0];
-            q = fma(a[i][1], vc[1], q);
-            q = fma(a[i][2], vc[2], q);
-            q = fma(a[i][3], vc[3], q);
-            if (G == 8) q += row_ror<8>(q);
-            if (G <= 16) q = add_row16(q);
-            pr[i] = add_row32(q);
-        }
-        if (lane < G) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) part[wv * NP + 4 * r + i] = pr[i];
-        }
-        __syncthreads();
-        for (int i = tid; i < NP; i += NT) {
-            double q = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) q += part[w * NP + i];
-            p[i] = q;
-        }
-        __syncthreads();
-        double K = 0.0;
-        for (int i = lane; i < NP; i += 64) K += vel(i) * p[i];
-        K = sum_wave(K);
-        double wr[4], wc[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            wr[i] = 2.0 * (p[4 * r + i] - K * vr[i]);
-            wc[i] = 2.0 * (p[4 * c + i] - K * vc[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a[i][j] -= vr[i] * wc[j] + wr[i] * vc[j];
     }
     if (r == c) {
 #pragma unroll
@@ -494,8 +545,11 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
         dT[i] = sd[i];
         eT[i] = se[i];
     }
-    // lowest eigenvalue of T: Gershgorin bounds, then multisection
+    // The lowest eigenpair of T by the first wave (the others go on to Q):
+    // Gershgorin bounds, multisection, twisted factorisation.  The chains
+    // read their operands eight steps at a time, ahead of the arithmetic.
     if (tid < 64) {
+        __builtin_amdgcn_s_setprio(3);
         double lo = 1e300, hi = -1e300;
         for (int i = lane; i < n; i += 64) {
             const double q = (i > 0 ? fabs(se[i - 1]) : 0.0) + fabs(se[i]);
@@ -507,51 +561,50 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
             lo = fmin(lo, __shfl_xor(lo, o, 64));
             hi = fmax(hi, __shfl_xor(hi, o, 64));
         }
-        if (lane == 0) {
-            sh[0] = lo;
-            sh[1] = hi;
+        // T in units of scale (p: diagonal, x: subdiagonal, x2: its square,
+        // one row later); the rows past n decouple, above the spectrum
+        double *x2 = x + NP;
+        const double scale = fmax(hi - lo + fabs(lo), 1e-30);
+        lo /= scale;
+        hi /= scale;
+        for (int i = lane; i < NP; i += 64) {
+            p[i] = i < n ? sd[i] / scale : lo + 2.0;
+            x[i] = i + 1 < n ? se[i] / scale : 0.0;
+            const double em = i > 0 && i < n ? se[i - 1] / scale : 0.0;
+            x2[i] = em * em;
         }
-    }
-    __syncthreads();
-    // T in units of scale (p: diagonal, x: subdiagonal and its square)
-    const double scale = fmax(sh[1] - sh[0] + fabs(sh[0]), 1e-30);
-    for (int i = tid; i < NP; i += NT) {
-        p[i] = sd[i] / scale;
-        x[i] = se[i] / scale;
-        x[NP + i] = x[i] * x[i];
-    }
-    double lo = sh[0] / scale, hi = sh[1] / scale;
-    __syncthreads();
-    for (int round = 0; round < 10 && hi - lo > 2e-16; ++round) {
-        const double y = lo + (hi - lo) * ((tid + 1) / (double)(NT + 1));
-        // T - y is positive definite iff every leading minor is positive; the
-        // pair of minors is scaled back every eight rows
-        double p0 = 1.0, p1 = p[0] - y;
-        bool pos = p1 > 0.0;
-        for (int i = 1; i < n; ++i) {
-            const double p2 = fma(p[i] - y, p1, -x[NP + i - 1] * p0);
-            p0 = p1;
-            p1 = p2;
-            pos = pos && p2 > 0.0;
-            if ((i & 7) == 0) {
+        wave_sync();
+        for (int round = 0; round < 10 && hi - lo > 2e-16; ++round) {
+            const double y = lo + (hi - lo) * ((lane + 1) / 65.0);
+            // T - y is positive definite iff every leading minor is positive; the
+            // pair of minors is scaled back every eight rows
+            double p0 = 0.0, p1 = 1.0;
+            int neg = 0;   // sign bits
+            for (int i0 = 0; i0 < n; i0 += 8) {
+                double dd[8], ee[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    dd[u] = p[i0 + u];
+                    ee[u] = x2[i0 + u];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const double p2 = fma(dd[u] - y, p1, -ee[u] * p0);
+                    p0 = p1;
+                    p1 = p2;
+                    neg |= __double2hiint(p2);
+                }
                 const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
                 p0 = __builtin_amdgcn_ldexp(p0, ex);
                 p1 = __builtin_amdgcn_ldexp(p1, ex);
             }
+            const int idx = __popcll(__ballot(neg >= 0));   // points below the lowest eigenvalue
+            const double nlo = idx > 0 ? lo + (hi - lo) * (idx / 65.0) : lo;
+            const double nhi = idx < 64 ? lo + (hi - lo) * ((idx + 1) / 65.0) : hi;
+            lo = nlo;
+            hi = nhi;
         }
-        const uint64_t mk = __ballot(pos);
-        if (lane == 0) wcnt[wv] = __popcll(mk);
-        __syncthreads();
-        int idx = 0;   // points below the lowest eigenvalue
-        for (int w = 0; w < NW; ++w) idx += wcnt[w];
-        __syncthreads();
-        const double nlo = idx > 0 ? lo + (hi - lo) * (idx / (double)(NT + 1)) : lo;
-        const double nhi = idx < NT ? lo + (hi - lo) * ((idx + 1) / (double)(NT + 1)) : hi;
-        lo = nlo;
-        hi = nhi;
-    }
-    // twisted factorisation of T - lo, by the first wave
-    if (tid < 64) {
+        // twisted factorisation of T - lo
         auto keep = [](double q) { return fabs(q) < 1e-18 ? (q >= 0.0 ? 1e-18 : -1e-18) : q; };
         if (lane < 2) {
             // lane 0: pu_i = d_i - e_{i-1}^2 / pu_{i-1}; lane 1: pl_i = d_i - e_i^2 / pl_{i+1}
@@ -559,10 +612,19 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
             double *out = lane ? pl : pu;
             double q = keep(p[i0] - lo);
             out[i0] = q;
-            for (int s = 1; s < n; ++s) {
-                const int i = i0 + st * s;
-                q = keep(fma(-x[NP + (lane ? i : i - 1)], fast_rcp(q), p[i] - lo));
-                out[i] = q;
+            for (int s0 = 1; s0 < n; s0 += 8) {
+                double dd[8], ee[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int i = i0 + st * min(s0 + u, n - 1);
+                    dd[u] = p[i] - lo;
+                    ee[u] = x2[i + lane];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    q = keep(fma(-ee[u], fast_rcp(q), dd[u]));
+                    if (s0 + u < n) out[i0 + st * (s0 + u)] = q;
+                }
             }
         }
         wave_sync();
@@ -585,27 +647,64 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
             }
         }
         wave_sync();
-        for (int i = lane; i < n; i += 64) {   // reciprocals, and multipliers towards the ends
+        // reciprocals, and multipliers towards the ends (x2: downwards pivots, pl: upwards)
+        for (int i = lane; i < n; i += 64) {
             pu[i] = fast_rcp(pu[i]);
+            x2[i] = -x[i] * pu[i];
             pl[i] = i > 0 ? -x[i - 1] * fast_rcp(pl[i]) : 0.0;
         }
         wave_sync();
-        if (lane == 0) {
+        if (lane < 2) {   // lane 0: rows above kb, upwards; lane 1: rows below, downwards
+            const int st = lane ? 1 : -1, len = lane ? n - 1 - kb : kb, top = max(kb, n - 1 - kb);
+            const double *f = lane ? pl : x2;
             double q = 1.0;
-            z[kb] = q;
-            for (int i = kb - 1; i >= 0; --i) z[i] = q = -x[i] * pu[i] * q;
-        } else if (lane == 1) {
-            double q = 1.0;
-            for (int i = kb + 1; i < n; ++i) z[i] = q = pl[i] * q;
+            if (lane == 0) z[kb] = q;
+            for (int s0 = 1; s0 <= top; s0 += 8) {
+                double ff[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) ff[u] = f[kb + st * min(s0 + u, len)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    q *= ff[u];
+                    if (s0 + u <= len) z[kb + st * (s0 + u)] = q;
+                }
+            }
         }
         wave_sync();
         // one step of inverse iteration on it: the twisted vector still holds
         // the other eigenvectors to |lambda - lo| / gap
         if (lane == 0) {
-            double q = z[0];
-            for (int i = 1; i < n; ++i) z[i] = q = fma(-x[i - 1] * pu[i - 1], q, z[i]);
-            z[n - 1] = q = z[n - 1] * pu[n - 1];
-            for (int i = n - 2; i >= 0; --i) z[i] = q = fma(-x[i], q, z[i]) * pu[i];
+            double q = 0.0;
+            for (int i0 = 0; i0 < n; i0 += 8) {   // (1 - x2 S) z, scaled by the pivots
+                double ff[8], zz[8], rr[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int i = min(i0 + u, n - 1);
+                    ff[u] = i > 0 ? x2[i - 1] : 0.0;
+                    zz[u] = z[i];
+                    rr[u] = pu[i];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    q = fma(ff[u], q, zz[u]);
+                    if (i0 + u < n) z[i0 + u] = q * rr[u];
+                }
+            }
+            q = 0.0;
+            for (int s0 = 0; s0 < n; s0 += 8) {
+                double ff[8], zz[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int i = max(n - 1 - s0 - u, 0);
+                    ff[u] = x2[i];
+                    zz[u] = z[i];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    q = fma(ff[u], q, zz[u]);
+                    if (s0 + u < n) z[n - 1 - s0 - u] = q;
+                }
+            }
         }
         wave_sync();
         double big = 0.0;
@@ -622,6 +721,7 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
         for (int i = lane; i < n; i += 64) nz += z[i] * z[i];
         nz = 1.0 / sqrt(sum_wave(nz));
         for (int i = lane; i < n; i += 64) z[i] *= nz;
+        __builtin_amdgcn_s_setprio(0);
     }
     // Q, column cq: H_k applied for k = n - 3 .. 0 to the unit vector; lane j
     // of the column's LPC lanes holds the row pairs 2 (j + LPC m), 2 (j + LPC m) + 1
@@ -634,27 +734,40 @@ __global__ __launch_bounds__(PspFactor<NP>::NT) void k_psp_factor(Batch b) {
     }
     // (columns up to k of the product are still unit vectors orthogonal to v_k)
     const int ctop = ((wv << 6) + 63) / LPC;   // the wave's last column
-    for (int k = n - 3; k >= 0; --k) {
-        if (k >= ctop) continue;
-        const dbl2v *v = reinterpret_cast<const dbl2v *>(V + k * NP) + j;
-        dbl2v vv[8];
-        double s = 0.0;
+    // (v_k is zero up to row k: the rows go in eight chunks, those of the
+    // reflections of one range of k start at chunk MB)
+    auto apply = [&](auto mb) {
+        constexpr int MB = decltype(mb)::value, CH = 2 * LPC;
+        for (int k = min(min(n - 3, ctop - 1), (MB + 1) * CH - 2); k >= 0 && k >= MB * CH - 1; --k) {
+            const dbl2v *v = reinterpret_cast<const dbl2v *>(V + k * NP) + j;
+            dbl2v vv[8];
+            double s = 0.0, s1 = 0.0;
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            vv[m] = v[LPC * m];
-            s = fma(vv[m].x, q0[m], s);
-            s = fma(vv[m].y, q1[m], s);
-        }
-        s += dpp_move<0xB1>(s);                    // lane ^ 1
-        if (LPC >= 4) s += dpp_move<0x4E>(s);      // lane ^ 2
-        if (LPC >= 8) s += dpp_move<0x141>(s);     // the other half of eight lanes
-        s *= -2.0;
+            for (int m = MB; m < 8; ++m) {
+                vv[m] = v[LPC * m];
+                s = fma(vv[m].x, q0[m], s);
+                s1 = fma(vv[m].y, q1[m], s1);
+            }
+            s += s1;
+            s += dpp_move<0xB1>(s);                    // lane ^ 1
+            if (LPC >= 4) s += dpp_move<0x4E>(s);      // lane ^ 2
+            if (LPC >= 8) s += dpp_move<0x141>(s);     // the other half of eight lanes
+            s *= -2.0;
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            q0[m] = fma(s, vv[m].x, q0[m]);
-            q1[m] = fma(s, vv[m].y, q1[m]);
+            for (int m = MB; m < 8; ++m) {
+                q0[m] = fma(s, vv[m].x, q0[m]);
+                q1[m] = fma(s, vv[m].y, q1[m]);
+            }
         }
-    }
+    };
+    apply(std::integral_constant<int, 7>{});
+    apply(std::integral_constant<int, 6>{});
+    apply(std::integral_constant<int, 5>{});
+    apply(std::integral_constant<int, 4>{});
+    apply(std::integral_constant<int, 3>{});
+    apply(std::integral_constant<int, 2>{});
+    apply(std::integral_constant<int, 1>{});
+    apply(std::integral_constant<int, 0>{});
     double *gQt = b.pQt + (int64_t)t * kPsp * kPsp;
     if (cq < n) {
 #pragma unroll
