@@ -128,52 +128,91 @@ __global__ __launch_bounds__(256) void k_sigma_g(Batch b, VecRef cref, VecRef sr
 // strip kernel (strip.hip); the string Hamiltonians H_s and their GEMMs
 // follow here.
 
-// Dense string Hamiltonian of one spin (symmetric, N x N per tuple); lane r
-// of a block accumulates row J = J0 + r in LDS:
-//   H e_J = sum_{links (Q,K,s) of J} s [ k_Q e_K + 1/2 sum_{links (P,I,s') of K} s' (P|Q) e_I ].
-// Only that lane adds into its row, by LDS atomic adds issued in program
-// order, so every entry is summed in the link order; the block then writes
-// its rows out coalesced.  rows = rows per block (dynamic LDS rows * N doubles).
-__global__ __launch_bounds__(64) void k_build_h(Batch b, int beta, int rows) {
-    const int t = blockIdx.y, lane = threadIdx.x;
-    const int64_t N = beta ? b.Nb : b.Na;
-    const int nent = beta ? b.nentB : b.nentA;
-    const uint32_t *links = beta ? b.linkB : b.linkA;
-    const int64_t J0 = (int64_t)blockIdx.x * rows;
-    const int nr = (int)(N - J0 < rows ? N - J0 : rows);
-    extern __shared__ double hrow[];   // [rows][N]
-    for (int64_t i = lane; i < (int64_t)nr * N; i += 64) hrow[i] = 0.0;
-    __syncthreads();
-    if (lane < nr) {
-        const ParamLayout &pl = b.pl;
-        const double *prm = b.params + (int64_t)t * pl.stride;
-        auto add = [&](int64_t col, double v) {
-            __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double *)(hrow + lane * N + col), v);
-        };
-        const uint32_t *lj = links + (J0 + lane) * nent;
-        for (int e = 0; e < nent; ++e) {
-            int K, Q;
-            double sg;
-            link_decode(lj[e], K, Q, sg);
-            add(K, sg * prm[pl.off_k + Q]);
-            const uint32_t *lk = links + (int64_t)K * nent;
-            for (int f = 0; f < nent; ++f) {
-                int I, P;
-                double s2;
-                link_decode(lk[f], I, P, s2);
-                add(I, sg * s2 * prm[pl.off_eri + P * pl.Kpad + Q]);   // stored as 1/2 (P|Q)
-            }
-        }
+// Dense string Hamiltonian of one spin (symmetric, N x N per tuple), every
+// element by the Slater-Condon rules from the two occupation masks:
+//   diagonal   sum_i h_ii + 1/2 sum_ij [(ii|jj) - (ij|ji)] over the occupied,
+//   p <- q     s [ k_pq + 1/2 sum_{r empty in both, or p, q} (pr|rq)
+//                  + sum_{j in both} ((pq|jj) - 1/2 (pj|jq)) ]
+//              (k_pq holds -1/2 sum_r (pr|rq) over all active r),
+//   p1 p2 <- q1 q2   s [ (p1 q1|p2 q2) - (p1 q2|p2 q1) ],
+// zero beyond two excitations.  A row per wave, its columns by the lanes, the
+// pair integrals in LDS: bound by the integer work on the masks.  It replaced
+// the sum over links of links, one row per lane in LDS, which ran no faster
+// than a lane's chain of n_links^2 adds: 792 strings of 5 in 12 orbitals 192 ->
+// 30 us, 20 strings 19 -> 5.7 us, 455 tuples of 84 strings among a sweep's
+// classes 92 -> 18 us on average.
+__global__ __launch_bounds__(256) void k_build_h(Batch b, int beta, int rows) {
+    const int t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const ParamLayout &pl = b.pl;
+    const int nA = b.nA, ld = pl.Kpad;
+    const uint32_t N = (uint32_t)(beta ? b.Nb : b.Na);
+    const uint32_t *str = beta ? b.strB : b.strA;
+    const double *prm = b.params + (int64_t)t * pl.stride;
+    extern __shared__ double lds[];
+    double *eri = lds;                 // [P][Kpad] 1/2 (P|Q)
+    double *kq = eri + pl.P * ld;      // [P]
+    double *hd = kq + pl.P;            // [nA] h^eff_ii
+    double *J = hd + nA, *K = J + nA * nA;   // (ii|jj), (ij|ji)
+    for (int i = tid; i < pl.P * ld; i += 256) eri[i] = prm[pl.off_eri + i];
+    for (int i = tid; i < pl.P; i += 256) kq[i] = prm[pl.off_k + i];
+    for (int i = tid; i < nA; i += 256) hd[i] = prm[pl.off_hd1 + i];
+    for (int i = tid; i < nA * nA; i += 256) {
+        J[i] = prm[pl.off_J + i];
+        K[i] = prm[pl.off_K + i];
     }
     __syncthreads();
-    double *H = (beta ? b.Hb : b.Ha) + ((int64_t)t * N + J0) * N;
-    for (int64_t i = lane; i < (int64_t)nr * N; i += 64) H[i] = hrow[i];
+    auto pair = [](int p, int q) { return p > q ? p * (p + 1) / 2 + q : q * (q + 1) / 2 + p; };
+    auto odd = [](uint32_t m, int p, int q) {   // occupied orbitals of m strictly between p and q
+        const int lo = p < q ? p : q, hi = p < q ? q : p;
+        return __popc(m & ((1u << hi) - 1u) & ~((2u << lo) - 1u)) & 1;
+    };
+    const uint32_t r0 = (uint32_t)blockIdx.x * rows, r1 = min(r0 + (uint32_t)rows, N);
+    double *H = (beta ? b.Hb : b.Ha) + (int64_t)t * N * N;
+    for (uint32_t row = r0 + wv; row < r1; row += 4) {
+        const uint32_t mj = __builtin_amdgcn_readfirstlane(str[row]);
+        for (uint32_t col = lane; col < N; col += 64) {
+            const uint32_t mi = str[col], diff = mi ^ mj;
+            const int nd = __popc(diff);
+            double v = 0.0;
+            if (nd == 4) {
+                const uint32_t cr = mi & diff, an = mj & diff;   // created in I, annihilated from J
+                const int p1 = __ffs(cr) - 1, p2 = 31 - __clz(cr), q1 = __ffs(an) - 1, q2 = 31 - __clz(an);
+                const uint32_t mk = mj ^ (1u << q2) ^ (1u << p2);   // E_{p2 q2} J
+                v = 2.0 * (eri[pair(p1, q1) * ld + pair(p2, q2)] - eri[pair(p1, q2) * ld + pair(p2, q1)]);
+                if (odd(mj, p2, q2) ^ odd(mk, p1, q1)) v = -v;
+            } else if (nd == 2) {
+                const int p = __ffs(mi & diff) - 1, q = __ffs(mj & diff) - 1, pq = pair(p, q);
+                const uint32_t both = mi & mj;
+                v = kq[pq];
+                for (int r = 0; r < nA; ++r) {
+                    const double x = eri[pair(p, r) * ld + pair(r, q)];
+                    if ((both >> r) & 1u) v += 2.0 * eri[pq * ld + r * (r + 3) / 2] - x;
+                    else v += x;
+                }
+                if (odd(mj, p, q)) v = -v;
+            } else if (nd == 0) {
+                for (int i = 0; i < nA; ++i)
+                    if ((mi >> i) & 1u) {
+                        v += hd[i];
+                        for (int j = 0; j < i; ++j)
+                            if ((mi >> j) & 1u) v += J[i * nA + j] - K[i * nA + j];
+                    }
+            }
+            H[(int64_t)row * N + col] = v;
+        }
+    }
 }
 
-// rows per block: up to 64, at most 80 KB of LDS (two blocks per CU)
-static int build_h_rows(int64_t N) {
-    const int64_t r = (80 * 1024) / (8 * (N > 0 ? N : 1));
-    return (int)(r < 1 ? 1 : (r > 64 ? 64 : r));
+static size_t build_h_lds(const Batch &b) {
+    return sizeof(double) * ((size_t)b.pl.P * b.pl.Kpad + b.pl.P + b.nA + 2 * (size_t)b.nA * b.nA);
+}
+
+static void launch_build_h_spin(const Batch &b, int beta, int64_t N, hipStream_t s) {
+    // rows per block: enough to pay for the integrals' way into LDS, few
+    // enough for several blocks per CU
+    const int64_t want = N * b.B / 2048;
+    const int rows = (int)(want < 4 ? 4 : (want > 32 ? 32 : (want + 3) / 4 * 4));
+    hipLaunchKernelGGL(k_build_h, dim3((unsigned)((N + rows - 1) / rows), b.B), dim3(256), build_h_lds(b), s, b, beta, rows);
 }
 
 hipError_t launch_build_hb(const Batch &b, hipStream_t s) {
@@ -182,12 +221,8 @@ hipError_t launch_build_hb(const Batch &b, hipStream_t s) {
         const hipError_t e = launch_linked_a(b, s);
         if (e != hipSuccess) return e;
     }
-    const int rb = build_h_rows(b.Nb), ra = build_h_rows(b.Na);
-    hipLaunchKernelGGL(k_build_h, dim3((unsigned)((b.Nb + rb - 1) / rb), b.B), dim3(64), (size_t)rb * b.Nb * sizeof(double),
-                       s, b, 1, rb);
-    if (b.Ha != b.Hb)
-        hipLaunchKernelGGL(k_build_h, dim3((unsigned)((b.Na + ra - 1) / ra), b.B), dim3(64),
-                           (size_t)ra * b.Na * sizeof(double), s, b, 0, ra);
+    launch_build_h_spin(b, 1, b.Nb, s);
+    if (b.Ha != b.Hb) launch_build_h_spin(b, 0, b.Na, s);
     return hipGetLastError();
 }
 
