@@ -48,6 +48,11 @@ __device__ __forceinline__ const double *vref(const VecRef &r, int t, int64_t di
     return r.base + (int64_t)t * r.tstride + (int64_t)k * dim;
 }
 
+// E_core of tuple t where sigma is to hold H's full action (ecore), else 0.
+__device__ __forceinline__ double core_shift(const Batch &b, int t, int ecore) {
+    return ecore ? b.params[(int64_t)t * b.pl.stride + b.pl.off_ecore] : 0.0;
+}
+
 __device__ __forceinline__ void link_decode(uint32_t L, int &J, int &Q, double &sg) {
     J = (int)(L & 0xFFFFFu);
     Q = (int)((L >> 20) & 0x3FFu);

@@ -164,7 +164,7 @@ hipError_t init_strip_kernels();   // the same for the strip kernels (called by 
 // alpha-beta term of sigma (column strip, strip.hip): sig = X + shift c
 // (ev_mid, if given, is recorded after the MFMA kernel, before the gather of
 // the W-in-HBM form)
-hipError_t launch_strip(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s,
+hipError_t launch_strip(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s,
                         hipEvent_t ev_mid = nullptr);
 // which alpha-beta kernel launch_sigma runs for the batch (0 all pair rows,
 // 1 linked gathered, 2 linked resident, 3 linked with the vector-ALU
@@ -200,7 +200,7 @@ hipError_t launch_hdiag(const Batch &b, double *out, int64_t ostride, int add_ec
 // sigma = (H + shift) c; with `dots` and the column-strip variant the GEMM
 // also leaves the partial dots V_i . sig, i <= m, in partial blocks
 // 0 .. gemm_blocks(b) - 1 (sigma_fuses_dots)
-hipError_t launch_sigma(const Batch &b, VecRef c, VecRef sig, double shift, bool skip_done, bool dots,
+hipError_t launch_sigma(const Batch &b, VecRef c, VecRef sig, int ecore, bool skip_done, bool dots,
                         hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, hipEvent_t evg, hipEvent_t ev2);
 inline bool sigma_fuses_dots(const Batch &b) { return b.sigma_variant == SIGMA_STRIP; }
 int gemm_blocks(const Batch &b);

@@ -94,12 +94,13 @@ __global__ __launch_bounds__(256) void k_sigma_w(Batch b, VecRef cref, int tiles
     }
 }
 
-__global__ __launch_bounds__(256) void k_sigma_g(Batch b, VecRef cref, VecRef sref, double shift, int skip_done) {
+__global__ __launch_bounds__(256) void k_sigma_g(Batch b, VecRef cref, VecRef sref, int ecore, int skip_done) {
     const int t = blockIdx.y;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const double *w = b.W + (int64_t)t * b.pl.P * b.dim;
     const double *c = vref(cref, t, b.dim);
     double *sg_out = const_cast<double *>(vref(sref, t, b.dim));
+    const double shift = core_shift(b, t, ecore);
     for (int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; d < b.dim;
          d += (int64_t)gridDim.x * blockDim.x) {
         const int64_t Ka = d / b.Nb, Kb = d % b.Nb;
@@ -443,11 +444,11 @@ static hipError_t launch_sym_sigma(const Batch &b, VecRef c, VecRef sig, bool sk
     return hipGetLastError();
 }
 
-hipError_t launch_sigma(const Batch &b, VecRef c, VecRef sig, double shift, bool skip_done, bool dots,
+hipError_t launch_sigma(const Batch &b, VecRef c, VecRef sig, int ecore, bool skip_done, bool dots,
                         hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, hipEvent_t evg, hipEvent_t ev2) {
     if (b.sigma_variant == SIGMA_STRIP) {
         if (ev0) (void)hipEventRecord(ev0, s);
-        hipError_t e = launch_strip(b, c, sig, shift, skip_done ? 1 : 0, s, ev1);
+        hipError_t e = launch_strip(b, c, sig, ecore, skip_done ? 1 : 0, s, ev1);
         if (e != hipSuccess) return e;
         if (evg) (void)hipEventRecord(evg, s);
         // (before the GEMM, whose epilogue forms the Davidson dots of the final sigma)
@@ -472,7 +473,7 @@ hipError_t launch_sigma(const Batch &b, VecRef c, VecRef sig, double shift, bool
     if (ev1) (void)hipEventRecord(ev1, s);
     if (evg) (void)hipEventRecord(evg, s);
     dim3 grid(grid_for(b.dim, 256, 4096), b.B);
-    hipLaunchKernelGGL(k_sigma_g, grid, dim3(256), 0, s, b, c, sig, shift, skip_done ? 1 : 0);
+    hipLaunchKernelGGL(k_sigma_g, grid, dim3(256), 0, s, b, c, sig, ecore, skip_done ? 1 : 0);
     e = hipGetLastError();
     if (e == hipSuccess) e = launch_spin_sigma(b, c, sig, skip_done, s);
     if (e == hipSuccess) e = launch_sym_sigma(b, c, sig, skip_done, s);

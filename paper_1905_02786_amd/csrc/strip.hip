@@ -146,7 +146,7 @@ __device__ __forceinline__ double group_sums2(double a, double b) {
 // besides wave 0's diagonal sum.
 template <int NA>
 __global__ __launch_bounds__(64 * StripShape<NA>::MT) void k_sigma_strip(Batch b, VecRef cref, VecRef sref,
-                                                                          double shift, int skip_done) {
+                                                                          int ecore, int skip_done) {
     using S = StripShape<NA>;
     constexpr int P = S::P, KP = S::Kpad, DR = S::DR, KS = S::KS, NX = S::NX, XR = S::XR, NTH = S::NTH,
                   NI = S::NI, KQ = S::KQ, NXA = NX > 0 ? NX : 1;
@@ -400,6 +400,7 @@ __global__ __launch_bounds__(64 * StripShape<NA>::MT) void k_sigma_strip(Batch b
         step(K, accA, accB, eA, eB);
         step(K + 1, accB, accA, eB, eA);
     }
+    const double shift = core_shift(b, t, ecore);
     for (uint32_t i = tid; i < Na * kStrip; i += NTH) {
         const uint32_t row = i / kStrip, col = i % kStrip;
         if (B0 + col < Nb) {
@@ -523,7 +524,7 @@ hipError_t launch_linked_a(const Batch &b, hipStream_t s) {
 // come in string order, as in the all-pairs kernel.  Strings past the last
 // read clamped C rows and the discard table row.
 template <int NA>
-__global__ __launch_bounds__(256) void k_sigma_linked_gat(Batch b, VecRef cref, VecRef sref, double shift,
+__global__ __launch_bounds__(256) void k_sigma_linked_gat(Batch b, VecRef cref, VecRef sref, int ecore,
                                                       int skip_done) {
     constexpr int P = NA * (NA + 1) / 2, KP = (P + 3) / 4 * 4, KS = KP / 4, NID = (KP + 15) / 16;
     constexpr int RL = (KS + 1) / 2 * 8;   // A-table row length (linked_row_len)
@@ -691,6 +692,7 @@ __global__ __launch_bounds__(256) void k_sigma_linked_gat(Batch b, VecRef cref, 
         step(n, afA, afB, accA, accB, eA, raA, cbA);
         step(n + 1, afB, afA, accB, accA, eB, raB, cbB);
     }
+    const double shift = core_shift(b, t, ecore);
     for (uint32_t i = tid; i < Na * kStrip; i += 256) {
         const uint32_t row = i / kStrip, col = i % kStrip;
         if (B0 + col < Nb) {
@@ -726,7 +728,7 @@ __global__ __launch_bounds__(256) void k_sigma_linked_gat(Batch b, VecRef cref, 
 // MFMA output rows of a lane (linked_scat_pos).  Dummy strings (index N_a)
 // pad the last pair and the pairs past it.
 template <int NA>
-__global__ __launch_bounds__(768) void k_sigma_linked_res(Batch b, VecRef cref, VecRef sref, double shift,
+__global__ __launch_bounds__(768) void k_sigma_linked_res(Batch b, VecRef cref, VecRef sref, int ecore,
                                                           int skip_done) {
     constexpr int P = NA * (NA + 1) / 2, KP = (P + 3) / 4 * 4, KS = KP / 4;
     constexpr int RL = (KS + 1) / 2 * 8;                      // A-table row length (linked_row_len)
@@ -916,6 +918,7 @@ __global__ __launch_bounds__(768) void k_sigma_linked_res(Batch b, VecRef cref, 
             __syncthreads();
         }
     }
+    const double shift = core_shift(b, t, ecore);
     for (uint32_t i = tid; i < Na * kStrip; i += 768) {
         const uint32_t row = i / kStrip, col = i % kStrip;
         if (B0 + col < Nb) {
@@ -951,7 +954,7 @@ __global__ __launch_bounds__(768) void k_sigma_linked_res(Batch b, VecRef cref, 
 // slots), bit 31 the alpha link sign, in the order of the MFMA output rows of
 // a lane (linked_scat_pos).
 template <int NA>
-__global__ __launch_bounds__(512) void k_sigma_linked_dv(Batch b, VecRef cref, VecRef sref, double shift,
+__global__ __launch_bounds__(512) void k_sigma_linked_dv(Batch b, VecRef cref, VecRef sref, int ecore,
                                                          int skip_done) {
     constexpr int P = NA * (NA + 1) / 2, KP = (P + 3) / 4 * 4, KS = KP / 4;
     constexpr int RL = (KS + 1) / 2 * 8;                      // A-table row length (linked_row_len)
@@ -1156,6 +1159,7 @@ __global__ __launch_bounds__(512) void k_sigma_linked_dv(Batch b, VecRef cref, V
         run(BoolC<true>{});
     else
         run(BoolC<false>{});
+    const double shift = core_shift(b, t, ecore);
     for (uint32_t i = tid; i < Na * kStrip; i += 512) {
         const uint32_t row = i / kStrip, col = i % kStrip;
         if (B0 + col < Nb) {
@@ -1348,7 +1352,7 @@ __global__ __launch_bounds__(256) void k_linked_wr(Batch b, VecRef cref, int ski
     }
 }
 
-// Gather: sigma(J, I_b) = sum_i sign_i W(row_i)(I_b) + shift c(J, I_b) over the
+// Gather: sigma(J, I_b) = sum_i sign_i W(row_i)(I_b) + E_core c(J, I_b) over the
 // incoming rows of J (table linc [N_a][ninc]: W row index K * SW + slot, bit
 // 31 the link sign; entry 0 is J's own diagonal-sum row), in table order.
 // One block per (512 columns, target string, tuple), two columns per thread
@@ -1356,7 +1360,7 @@ __global__ __launch_bounds__(256) void k_linked_wr(Batch b, VecRef cref, int ski
 // aligned); the table row is staged in LDS and all loads of a column pair
 // are issued before the ordered sum.
 template <bool V2>
-__global__ __launch_bounds__(256) void k_linked_gw(Batch b, VecRef cref, VecRef sref, double shift, int skip_done) {
+__global__ __launch_bounds__(256) void k_linked_gw(Batch b, VecRef cref, VecRef sref, int ecore, int skip_done) {
     const int t = blockIdx.z;
     if (skip_done && b.status[t] != ST_RUNNING) return;
     const uint32_t J = blockIdx.y, Nb = (uint32_t)b.Nb;
@@ -1366,6 +1370,7 @@ __global__ __launch_bounds__(256) void k_linked_gw(Batch b, VecRef cref, VecRef 
     __syncthreads();
     const uint32_t ib = blockIdx.x * 512u + 2u * threadIdx.x;
     if (ib >= Nb) return;
+    const double shift = core_shift(b, t, ecore);
     const double *W = b.lw + (int64_t)t * b.lw_stride;
     const double *c = vref(cref, t, b.dim);
     double *sg = const_cast<double *>(vref(sref, t, b.dim));
@@ -1418,7 +1423,7 @@ bool linked_w_fits(const ParamLayout &pl, int64_t Na, int nel) {
 }
 
 template <int NA>
-static hipError_t launch_linked_w_na(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s,
+static hipError_t launch_linked_w_na(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s,
                                      hipEvent_t ev_mid) {
     const int64_t nstrips = (b.Nb + kStrip - 1) / kStrip;
     // two workgroups run per CU: small batches split the strings of a strip
@@ -1431,8 +1436,8 @@ static hipError_t launch_linked_w_na(const Batch &b, VecRef c, VecRef sig, doubl
     if (e != hipSuccess) return e;
     if (ev_mid) (void)hipEventRecord(ev_mid, s);
     const dim3 gg((unsigned)((b.Nb + 511) / 512), (unsigned)b.Na, (unsigned)b.B);
-    if ((b.Nb & 1) == 0) hipLaunchKernelGGL(k_linked_gw<true>, gg, dim3(256), 0, s, b, c, sig, shift, skip);
-    else hipLaunchKernelGGL(k_linked_gw<false>, gg, dim3(256), 0, s, b, c, sig, shift, skip);
+    if ((b.Nb & 1) == 0) hipLaunchKernelGGL(k_linked_gw<true>, gg, dim3(256), 0, s, b, c, sig, ecore, skip);
+    else hipLaunchKernelGGL(k_linked_gw<false>, gg, dim3(256), 0, s, b, c, sig, ecore, skip);
     return hipGetLastError();
 }
 
@@ -1459,84 +1464,84 @@ int alpha_beta_kernel(const Batch &b) {
 }
 
 template <int NA>
-static hipError_t launch_linked_na(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s) {
+static hipError_t launch_linked_na(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s) {
     const int64_t nstrips = (b.Nb + kStrip - 1) / kStrip;
     const dim3 grid((unsigned)(b.B * nstrips));
     if (b.linked_dv)
-        hipLaunchKernelGGL(k_sigma_linked_dv<NA>, grid, dim3(512), linked_lds_dv(b.pl, b.Na), s, b, c, sig, shift,
+        hipLaunchKernelGGL(k_sigma_linked_dv<NA>, grid, dim3(512), linked_lds_dv(b.pl, b.Na), s, b, c, sig, ecore,
                            skip);
     else if (use_resident(b))
         hipLaunchKernelGGL(k_sigma_linked_res<NA>, grid, dim3(768), linked_lds_res(b.pl, b.Na), s, b, c, sig,
-                           shift, skip);
+                           ecore, skip);
     else
         hipLaunchKernelGGL(k_sigma_linked_gat<NA>, grid, dim3(256), linked_lds_gat(b.pl, b.Na), s, b, c, sig,
-                           shift, skip);
+                           ecore, skip);
     return hipGetLastError();
 }
 
 template <int NA>
-static hipError_t launch_strip_na(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s) {
+static hipError_t launch_strip_na(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s) {
     const int64_t nstrips = (b.Nb + kStrip - 1) / kStrip;
     const dim3 grid((unsigned)(b.B * nstrips));
     hipLaunchKernelGGL(k_sigma_strip<NA>, grid, dim3(StripShape<NA>::NTH), strip_lds(b.pl, b.Na), s, b, c, sig,
-                       shift, skip);
+                       ecore, skip);
     return hipGetLastError();
 }
 
-static hipError_t launch_strip_one(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s);
+static hipError_t launch_strip_one(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s);
 
-hipError_t launch_strip(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s,
+hipError_t launch_strip(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s,
                         hipEvent_t ev_mid) {
     if (b.lw) {   // linked rows through W in HBM (the planner checked linked_w_fits)
         switch (b.nA) {
-            case 4: return launch_linked_w_na<4>(b, c, sig, shift, skip, s, ev_mid);
-            case 5: return launch_linked_w_na<5>(b, c, sig, shift, skip, s, ev_mid);
-            case 6: return launch_linked_w_na<6>(b, c, sig, shift, skip, s, ev_mid);
-            case 7: return launch_linked_w_na<7>(b, c, sig, shift, skip, s, ev_mid);
-            case 8: return launch_linked_w_na<8>(b, c, sig, shift, skip, s, ev_mid);
-            case 9: return launch_linked_w_na<9>(b, c, sig, shift, skip, s, ev_mid);
-            case 10: return launch_linked_w_na<10>(b, c, sig, shift, skip, s, ev_mid);
-            case 11: return launch_linked_w_na<11>(b, c, sig, shift, skip, s, ev_mid);
-            case 12: return launch_linked_w_na<12>(b, c, sig, shift, skip, s, ev_mid);
-            case 13: return launch_linked_w_na<13>(b, c, sig, shift, skip, s, ev_mid);
+            case 4: return launch_linked_w_na<4>(b, c, sig, ecore, skip, s, ev_mid);
+            case 5: return launch_linked_w_na<5>(b, c, sig, ecore, skip, s, ev_mid);
+            case 6: return launch_linked_w_na<6>(b, c, sig, ecore, skip, s, ev_mid);
+            case 7: return launch_linked_w_na<7>(b, c, sig, ecore, skip, s, ev_mid);
+            case 8: return launch_linked_w_na<8>(b, c, sig, ecore, skip, s, ev_mid);
+            case 9: return launch_linked_w_na<9>(b, c, sig, ecore, skip, s, ev_mid);
+            case 10: return launch_linked_w_na<10>(b, c, sig, ecore, skip, s, ev_mid);
+            case 11: return launch_linked_w_na<11>(b, c, sig, ecore, skip, s, ev_mid);
+            case 12: return launch_linked_w_na<12>(b, c, sig, ecore, skip, s, ev_mid);
+            case 13: return launch_linked_w_na<13>(b, c, sig, ecore, skip, s, ev_mid);
             default: return hipErrorInvalidValue;
         }
     }
-    hipError_t e = launch_strip_one(b, c, sig, shift, skip, s);
+    hipError_t e = launch_strip_one(b, c, sig, ecore, skip, s);
     if (e == hipSuccess && ev_mid) (void)hipEventRecord(ev_mid, s);
     return e;
 }
 
-static hipError_t launch_strip_one(const Batch &b, VecRef c, VecRef sig, double shift, int skip, hipStream_t s) {
+static hipError_t launch_strip_one(const Batch &b, VecRef c, VecRef sig, int ecore, int skip, hipStream_t s) {
     if (b.la) {   // linked-row variant (the planner checked linked_fits)
         switch (b.nA) {
-            case 4: return launch_linked_na<4>(b, c, sig, shift, skip, s);
-            case 5: return launch_linked_na<5>(b, c, sig, shift, skip, s);
-            case 6: return launch_linked_na<6>(b, c, sig, shift, skip, s);
-            case 7: return launch_linked_na<7>(b, c, sig, shift, skip, s);
-            case 8: return launch_linked_na<8>(b, c, sig, shift, skip, s);
-            case 9: return launch_linked_na<9>(b, c, sig, shift, skip, s);
-            case 10: return launch_linked_na<10>(b, c, sig, shift, skip, s);
-            case 11: return launch_linked_na<11>(b, c, sig, shift, skip, s);
-            case 12: return launch_linked_na<12>(b, c, sig, shift, skip, s);
-            case 13: return launch_linked_na<13>(b, c, sig, shift, skip, s);
+            case 4: return launch_linked_na<4>(b, c, sig, ecore, skip, s);
+            case 5: return launch_linked_na<5>(b, c, sig, ecore, skip, s);
+            case 6: return launch_linked_na<6>(b, c, sig, ecore, skip, s);
+            case 7: return launch_linked_na<7>(b, c, sig, ecore, skip, s);
+            case 8: return launch_linked_na<8>(b, c, sig, ecore, skip, s);
+            case 9: return launch_linked_na<9>(b, c, sig, ecore, skip, s);
+            case 10: return launch_linked_na<10>(b, c, sig, ecore, skip, s);
+            case 11: return launch_linked_na<11>(b, c, sig, ecore, skip, s);
+            case 12: return launch_linked_na<12>(b, c, sig, ecore, skip, s);
+            case 13: return launch_linked_na<13>(b, c, sig, ecore, skip, s);
             default: return hipErrorInvalidValue;
         }
     }
     switch (b.nA) {
-        case 1: return launch_strip_na<1>(b, c, sig, shift, skip, s);
-        case 2: return launch_strip_na<2>(b, c, sig, shift, skip, s);
-        case 3: return launch_strip_na<3>(b, c, sig, shift, skip, s);
-        case 4: return launch_strip_na<4>(b, c, sig, shift, skip, s);
-        case 5: return launch_strip_na<5>(b, c, sig, shift, skip, s);
-        case 6: return launch_strip_na<6>(b, c, sig, shift, skip, s);
-        case 7: return launch_strip_na<7>(b, c, sig, shift, skip, s);
-        case 8: return launch_strip_na<8>(b, c, sig, shift, skip, s);
-        case 9: return launch_strip_na<9>(b, c, sig, shift, skip, s);
-        case 10: return launch_strip_na<10>(b, c, sig, shift, skip, s);
-        case 11: return launch_strip_na<11>(b, c, sig, shift, skip, s);
-        case 12: return launch_strip_na<12>(b, c, sig, shift, skip, s);
-        case 13: return launch_strip_na<13>(b, c, sig, shift, skip, s);
+        case 1: return launch_strip_na<1>(b, c, sig, ecore, skip, s);
+        case 2: return launch_strip_na<2>(b, c, sig, ecore, skip, s);
+        case 3: return launch_strip_na<3>(b, c, sig, ecore, skip, s);
+        case 4: return launch_strip_na<4>(b, c, sig, ecore, skip, s);
+        case 5: return launch_strip_na<5>(b, c, sig, ecore, skip, s);
+        case 6: return launch_strip_na<6>(b, c, sig, ecore, skip, s);
+        case 7: return launch_strip_na<7>(b, c, sig, ecore, skip, s);
+        case 8: return launch_strip_na<8>(b, c, sig, ecore, skip, s);
+        case 9: return launch_strip_na<9>(b, c, sig, ecore, skip, s);
+        case 10: return launch_strip_na<10>(b, c, sig, ecore, skip, s);
+        case 11: return launch_strip_na<11>(b, c, sig, ecore, skip, s);
+        case 12: return launch_strip_na<12>(b, c, sig, ecore, skip, s);
+        case 13: return launch_strip_na<13>(b, c, sig, ecore, skip, s);
         default: return hipErrorInvalidValue;
     }
 }
