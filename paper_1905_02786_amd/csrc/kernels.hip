@@ -193,21 +193,28 @@ __device__ void store_block_partials(const Batch &b, int t, const double *acc, i
 // P selection, one block per tuple: histogram of H_II over [min, max] in 1024
 // bins, then the determinants of the bins below the one holding the psp-th
 // smallest value, and from that bin the lowest indices up to psp, in index
-// order (deterministic, ties broken by index).
-__global__ __launch_bounds__(256) void k_psp_select(Batch b) {
+// order (deterministic, ties broken by index).  Bound by the latency of one
+// workgroup's loads: sixteen waves, and for the last two passes a contiguous
+// range each, so that the places come from one prefix sum over the waves
+// (waves without a determinant of P skip the last pass).  245 025 to 853 776
+// determinants 4.0 -> 1.1 ms, 3136 to 15 876 39 -> 14 us, 120 to 1225 12 ->
+// 4 us a launch, against four waves and two barriers per 256 determinants.
+__global__ __launch_bounds__(1024) void k_psp_select(Batch b) {
+    constexpr int NW = 16, NT = 64 * NW;
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int n = b.psp;
     const double *hd = b.Hd + (int64_t)t * b.dim;
     int32_t *out = b.pidx + (int64_t)t * kPsp;
-    __shared__ double rmin[4], rmax[4];
-    __shared__ int hist[1024];
-    __shared__ int sB, sC0, sNeed, wc1[4], wc2[4];
+    __shared__ double rmin[NW], rmax[NW];
+    __shared__ int hist[1024], sum[1024 / 64];
+    __shared__ int sB, sC0, sNeed, wc1[NW], wc2[NW];
     if (b.dim <= n) {
-        for (int i = tid; i < n; i += 256) out[i] = i;
+        for (int i = tid; i < n; i += NT) out[i] = i;
         return;
     }
     double mn = 1e300, mx = -1e300;
-    for (int64_t d = tid; d < b.dim; d += 256) {
+#pragma unroll 4
+    for (int64_t d = tid; d < b.dim; d += NT) {
         mn = fmin(mn, hd[d]);
         mx = fmax(mx, hd[d]);
     }
@@ -220,83 +227,81 @@ __global__ __launch_bounds__(256) void k_psp_select(Batch b) {
         rmin[wv] = mn;
         rmax[wv] = mx;
     }
-    for (int i = tid; i < 1024; i += 256) hist[i] = 0;
+    hist[tid] = 0;
     __syncthreads();
-    mn = fmin(fmin(rmin[0], rmin[1]), fmin(rmin[2], rmin[3]));
-    mx = fmax(fmax(rmax[0], rmax[1]), fmax(rmax[2], rmax[3]));
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+        mn = fmin(mn, rmin[q]);
+        mx = fmax(mx, rmax[q]);
+    }
     const double scale = mx > mn ? 1024.0 / (mx - mn) : 0.0;
     auto bin = [&](double v) -> int {
         const int k = (int)((v - mn) * scale);
         return k < 0 ? 0 : (k > 1023 ? 1023 : k);
     };
-    for (int64_t d = tid; d < b.dim; d += 256) atomicAdd(&hist[bin(hd[d])], 1);
+#pragma unroll 4
+    for (int64_t d = tid; d < b.dim; d += NT) atomicAdd(&hist[bin(hd[d])], 1);
     __syncthreads();
-    if (tid == 0) {
-        int c = 0;
-        for (int k = 0; k < 1024; ++k) {
-            if (c + hist[k] >= n) {
-                sB = k;
-                sC0 = c;
-                sNeed = n - c;
-                break;
-            }
-            c += hist[k];
-        }
+    // the first bin where the running count reaches n
+    int inc = hist[tid];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) sum[wv] = inc;
+    __syncthreads();
+    for (int q = 0; q < wv; ++q) inc += sum[q];
+    if (inc >= n && inc - hist[tid] < n) {
+        sB = tid;
+        sC0 = inc - hist[tid];
+        sNeed = n - (inc - hist[tid]);
     }
     __syncthreads();
     const int B = sB, C0 = sC0, need = sNeed;
-    int base1 = 0, base2 = 0;
-    for (int64_t d0 = 0; d0 < b.dim; d0 += 256) {
-        const int64_t d = d0 + tid;
-        const int k = d < b.dim ? bin(hd[d]) : 2048;
+    const int64_t len = ((b.dim + NT - 1) / NT) * 64, d0 = wv * len, d1 = d0 + len < b.dim ? d0 + len : b.dim;
+    int c1 = 0, c2 = 0;
+#pragma unroll 4
+    for (int64_t d = d0 + lane; d < d1; d += 64) {
+        const int k = bin(hd[d]);
+        c1 += k < B;
+        c2 += k == B;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        c1 += __shfl_xor(c1, o, 64);
+        c2 += __shfl_xor(c2, o, 64);
+    }
+    if (lane == 0) {
+        wc1[wv] = c1;
+        wc2[wv] = c2;
+    }
+    __syncthreads();
+    int o1 = 0, o2 = 0;
+    for (int q = 0; q < wv; ++q) {
+        o1 += wc1[q];
+        o2 += wc2[q];
+    }
+    if (c1 == 0 && (c2 == 0 || o2 >= need)) return;
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+    for (int64_t e = d0; e < d1; e += 64) {
+        const int64_t d = e + lane;
+        const int k = d < d1 ? bin(hd[d]) : 2048;
         const bool f1 = k < B, f2 = k == B;
         const uint64_t m1 = __ballot(f1), m2 = __ballot(f2);
-        const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-        const int p1 = __popcll(m1 & below), p2 = __popcll(m2 & below);
-        if (lane == 0) {
-            wc1[wv] = __popcll(m1);
-            wc2[wv] = __popcll(m2);
-        }
-        __syncthreads();
-        int o1 = base1, o2 = base2, t1 = 0, t2 = 0;
-        for (int q = 0; q < 4; ++q) {
-            if (q < wv) {
-                o1 += wc1[q];
-                o2 += wc2[q];
-            }
-            t1 += wc1[q];
-            t2 += wc2[q];
-        }
-        if (f1) out[o1 + p1] = (int32_t)d;
-        if (f2 && o2 + p2 < need) out[C0 + o2 + p2] = (int32_t)d;
-        base1 += t1;
-        base2 += t2;
-        __syncthreads();
-        if (base1 >= C0 && base2 >= need) break;
+        const int p2 = o2 + __popcll(m2 & below);
+        if (f1) out[o1 + __popcll(m1 & below)] = (int32_t)d;
+        if (f2 && p2 < need) out[C0 + p2] = (int32_t)d;
+        o1 += __popcll(m1);
+        o2 += __popcll(m2);
     }
 }
 
-// One alpha (or beta) string pair <I|E+_P|J>: the pairs P with their
-// coefficients (diagonal: the occupied orbitals of I, coefficient 1; a single
-// excitation: its pair and sign; otherwise none).  Returns the count.
-__device__ __forceinline__ int string_transition(uint32_t mi, uint32_t mj, int *P, double *c) {
-    const uint32_t diff = mi ^ mj;
-    if (diff == 0u) {
-        int k = 0;
-        for (uint32_t x = mi; x; x &= x - 1) {
-            const int p = __ffs(x) - 1;
-            P[k] = p * (p + 3) / 2;
-            c[k++] = 1.0;
-        }
-        return k;
-    }
-    if (__popc(diff) != 2) return 0;
-    const int p = __ffs(mi & diff) - 1, q = __ffs(mj & diff) - 1;   // created in I, annihilated from J
+// Pair index of the single excitation between two strings.
+__device__ __forceinline__ int single_pair(uint32_t mi, uint32_t mj) {
+    const int p = __ffs(mi & ~mj) - 1, q = __ffs(mj & ~mi) - 1;
     const int lo = p < q ? p : q, hi = p < q ? q : p;
-    const uint32_t between = mj & (((1u << hi) - 1u) & ~((1u << (lo + 1)) - 1u));
-    P[0] = hi * (hi + 1) / 2 + lo;
-    c[0] = (__popc(between) & 1) ? -1.0 : 1.0;
-    return 1;
+    return hi * (hi + 1) / 2 + lo;
 }
 
 // Sign of the single excitation that turns string J into string I (one
@@ -330,22 +335,42 @@ __global__ __launch_bounds__(256) void k_psp_build(Batch b) {
         double v = 0.0;
         if (ib == jb) v += Ha[ia * b.Na + ja];
         if (ia == ja) v += Hb[ib * b.Nb + jb];
-        int Pa[kMaxActive], Pb[kMaxActive];
-        double ca[kMaxActive], cb2[kMaxActive];
-        const int na = string_transition(b.strA[ia], b.strA[ja], Pa, ca);
-        const int nb = na ? string_transition(b.strB[ib], b.strB[jb], Pb, cb2) : 0;
+        const uint32_t mia = b.strA[ia], mja = b.strA[ja], mib = b.strB[ib], mjb = b.strB[jb];
+        const int da = __popc(mia ^ mja), db = __popc(mib ^ mjb);
         double x = 0.0;
-        for (int u = 0; u < na; ++u)
-            for (int w2 = 0; w2 < nb; ++w2) x += ca[u] * cb2[w2] * prm[pl.off_eri + Pa[u] * pl.Kpad + Pb[w2]];
+        if (da <= 2 && db <= 2) {
+            const double *e = prm + pl.off_eri;
+            const int P = da ? single_pair(mia, mja) : 0, Q = db ? single_pair(mib, mjb) : 0;
+            if (da && db) {
+                x = e[P * pl.Kpad + Q];
+            } else if (da) {
+                for (uint32_t y = mib; y; y &= y - 1) {
+                    const int q = __ffs(y) - 1;
+                    x += e[P * pl.Kpad + q * (q + 3) / 2];
+                }
+            } else {
+                for (uint32_t z = mia; z; z &= z - 1) {
+                    const int p = __ffs(z) - 1;
+                    const double *ep = e + p * (p + 3) / 2 * pl.Kpad;
+                    if (db) x += ep[Q];
+                    else
+                        for (uint32_t y = mib; y; y &= y - 1) {
+                            const int q = __ffs(y) - 1;
+                            x += ep[q * (q + 3) / 2];
+                        }
+                }
+            }
+            if (da) x *= excitation_sign(mia, mja);
+            if (db) x *= excitation_sign(mib, mjb);
+        }
         v += 2.0 * x;   // stored as 1/2 (P|Q)
         if (b.sym_shift != 0.0 && I == J) v += sym_pen(b, t, b.strA[ia], b.strB[ib]);
         if (b.spin_shift != 0.0) {
-            const uint32_t mia = b.strA[ia], mja = b.strA[ja], mib = b.strB[ib], mjb = b.strB[jb];
             if (I == J) {
                 v += b.spin_shift * (double)(b.nb - __popc(mia & mib));
             } else {
-                const uint32_t da = mia ^ mja, db = mib ^ mjb;
-                if (__popc(da) == 2 && __popc(db) == 2 && (mia & da) == (mjb & db) && (mja & da) == (mib & db))
+                const uint32_t xa = mia ^ mja, xb = mib ^ mjb;
+                if (da == 2 && db == 2 && (mia & xa) == (mjb & xb) && (mja & xa) == (mib & xb))
                     v -= b.spin_shift * excitation_sign(mia, mja) * excitation_sign(mib, mjb);
             }
         }
@@ -809,8 +834,9 @@ template <int NP> static void launch_psp_factor(const Batch &b, hipStream_t s) {
 
 hipError_t launch_pspace(const Batch &b, hipStream_t s) {
     if (b.psp <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_psp_select, dim3(b.B), dim3(256), 0, s, b);
-    hipLaunchKernelGGL(k_psp_build, dim3(b.B, (b.psp * b.psp + 2047) / 2048), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(k_psp_select, dim3(b.B), dim3(1024), 0, s, b);
+    const int per = b.B > 64 ? 2048 : 512;   // elements per block: one block per CU or so for few tuples
+    hipLaunchKernelGGL(k_psp_build, dim3(b.B, (b.psp * b.psp + per - 1) / per), dim3(256), 0, s, b);
     if (b.psp <= 32) launch_psp_factor<32>(b, s);
     else if (b.psp <= 64) launch_psp_factor<64>(b, s);
     else launch_psp_factor<128>(b, s);
