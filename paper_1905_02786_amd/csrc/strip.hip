@@ -216,7 +216,9 @@ __global__ __launch_bounds__(64 * StripShape<NA>::MT) void k_sigma_strip(Batch b
         boff[i] = vb ? (eb & kPairJ) * (uint32_t)sizeof(double) : 0x80000000u;
         bsg[i] = vb ? (eb & kPairSign) : 0u;
         qa[i] = (uint32_t)(qi[i] < P ? qi[i] : P) * (uint32_t)sizeof(uint32_t);
-        dsl[i] = (uint32_t)(D + qi[i] * kStrip + ar - lds) * (uint32_t)sizeof(double);
+        // (the wave tiles' rows past P have no D row of their own: unclamped,
+        // their zeros would land in the other buffer, under its readers)
+        dsl[i] = (uint32_t)(D + (qi[i] < P ? qi[i] : P) * kStrip + ar - lds) * (uint32_t)sizeof(double);
     }
     for (uint32_t i = tid; i < (Na + 1) * kStrip; i += NTH) strip[i] = 0.0;
     for (int i = tid; i < 2 * DR * kStrip; i += NTH) D[i] = 0.0;

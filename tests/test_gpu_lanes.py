@@ -99,3 +99,16 @@ def test_gradient(ws):
     assert g[0][0] == g[1][0]
     for a, b in zip(g[0][1:], g[1][1:]):
         assert np.abs(a - b).max() <= 1e-12
+
+
+def test_repeats_are_bitwise(ws):
+    # every sigma form of the plain expansion beside the others: a wave that
+    # falls behind must not change what it or its neighbours read
+    P = PROBLEMS["plain"]()
+    lists = [(k, list(itertools.combinations(P.expansion_space(), k))) for k in (5, 6, 7)]
+    ctx = M.Context.from_problem(P, device=0)
+    mn = max(ctx.workspace_query(k, tl)[0] for k, tl in lists)
+    ref = [ctx.solve_tuples(k, tl, M.workspace(mn))[0] for k, tl in lists]
+    for rep in range(60):
+        for (k, tl), r in zip(lists, ref):
+            assert np.array_equal(ctx.solve_tuples(k, tl, ws)[0], r), (rep, k)
