@@ -107,8 +107,8 @@ def test_repeats_are_bitwise(ws):
     P = PROBLEMS["plain"]()
     lists = [(k, list(itertools.combinations(P.expansion_space(), k))) for k in (5, 6, 7)]
     ctx = M.Context.from_problem(P, device=0)
-    mn = max(ctx.workspace_query(k, tl)[0] for k, tl in lists)
-    ref = [ctx.solve_tuples(k, tl, M.workspace(mn))[0] for k, tl in lists]
+    small = M.workspace(8 << 20)   # (one tuple of the largest, in the form that needs most)
+    ref = [ctx.solve_tuples(k, tl, small)[0] for k, tl in lists]
     for rep in range(60):
         for (k, tl), r in zip(lists, ref):
             assert np.array_equal(ctx.solve_tuples(k, tl, ws)[0], r), (rep, k)
