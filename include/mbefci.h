@@ -447,8 +447,10 @@ mbefci_status mbefci_backward(mbefci_ctx *ctx, const mbefci_result *res, double 
  * null): U [n*n] row-major (column j = new orbital j in the orbitals the
  * Hamiltonian had on entry), the CASSCF energy, the steps taken.  ENOCONV if
  * g_tol is not reached in max_iter steps (the Hamiltonian is then replaced
- * by the canonical form of the last orbitals); ETOOLARGE for a reference space
- * of more than 12 orbitals; ENOMEM if the workspace is too small. */
+ * by the canonical form of the last orbitals) or if a trial CASCI does not
+ * converge (the Hamiltonian is then as it was on entry); ETOOLARGE for a
+ * reference space of more than 12 orbitals; ENOMEM if the workspace is too
+ * small.  After EDEVICE the Hamiltonian is as it was or has to be set again. */
 mbefci_status mbefci_casscf(mbefci_ctx *ctx, void *d_workspace, size_t ws_bytes, int32_t max_iter, double g_tol,
                             double *U, double *energy, int32_t *iterations);
 

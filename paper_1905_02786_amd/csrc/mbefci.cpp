@@ -2609,6 +2609,31 @@ mbefci_status mbefci_backward(mbefci_ctx *ctx, const mbefci_result *res, double 
     return MBEFCI_OK;
 }
 
+// The context's integrals on the device while an orbital optimisation puts
+// trial ones in their place: unless it ends with done(), they are the starting
+// ones again (h0, eri0, the routine's copies), as the host's still are.  Once
+// the host's are being replaced too (host), or where the copies back fail,
+// neither can be trusted: the Hamiltonian has to be set again.
+namespace {
+struct TrialIntegrals {
+    mbefci_ctx *ctx;
+    const double *h0, *eri0;
+    bool host = false, armed = true;
+    TrialIntegrals(mbefci_ctx *c, const double *h, const double *eri) : ctx(c), h0(h), eri0(eri) {}
+    TrialIntegrals(const TrialIntegrals &) = delete;
+    TrialIntegrals &operator=(const TrialIntegrals &) = delete;
+    void done() { armed = false; }
+    ~TrialIntegrals() {
+        if (!armed) return;
+        const size_t n2 = (size_t)ctx->norb * ctx->norb;
+        hipError_t e = hipMemcpyAsync(ctx->d_h, h0, 8 * n2, hipMemcpyDeviceToDevice, ctx->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(ctx->d_eri, eri0, 8 * n2 * n2, hipMemcpyDeviceToDevice, ctx->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess || host) ctx->ham_set = false;
+    }
+};
+}  // namespace
+
 mbefci_status mbefci_casscf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter, double g_tol, double *U_out,
                             double *e_out, int32_t *iter_out) {
     if (!ctx) return MBEFCI_EINVAL;
@@ -2653,6 +2678,7 @@ mbefci_status mbefci_casscf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_i
     HIPCHK(hipMemcpyAsync(d_eri0, ctx->eri.data(), 8 * n4, hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(d_h0, ctx->h.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(d_occ, occ.data(), 4 * occ.size(), hipMemcpyHostToDevice, ctx->stream));
+    TrialIntegrals trial(ctx, d_h0, d_eri0);
     // the reference CASCI converged tightly: the gradient comes from its
     // density matrices, which carry the residual to first order
     const mbefci_options saved = ctx->opt;
@@ -2844,6 +2870,7 @@ mbefci_status mbefci_casscf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_i
     HIPCHK(hipMemcpyAsync(d_U, Uc.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
     hipError_t e = launch_rotate_integrals(d_h0, d_eri0, d_U, ctx->d_h, ctx->d_eri, d_tmp, n, ctx->stream);
     if (e != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
+    trial.host = true;
     HIPCHK(hipMemcpyAsync(ctx->h.data(), ctx->d_h, 8 * n2, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipMemcpyAsync(ctx->eri.data(), ctx->d_eri, 8 * n4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
@@ -2853,6 +2880,7 @@ mbefci_status mbefci_casscf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_i
             ctx->h[(size_t)p * n + q] = ctx->h[(size_t)q * n + p] = v;
         }
     HIPCHK(hipMemcpy(ctx->d_h, ctx->h.data(), 8 * n2, hipMemcpyHostToDevice));
+    trial.done();
     ctx->sym_checked = false;
     if (U_out) std::memcpy(U_out, Uc.data(), 8 * n2);
     if (e_out) *e_out = E;
@@ -2895,6 +2923,7 @@ mbefci_status mbefci_hf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter,
     const Mat h0 = ctx->h;
     HIPCHK(hipMemcpyAsync(d_eri0, ctx->d_eri, 8 * n4, hipMemcpyDeviceToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(d_h0, ctx->d_h, 8 * n2, hipMemcpyDeviceToDevice, ctx->stream));
+    TrialIntegrals trial(ctx, d_h0, d_eri0);
     // energy and the Fock matrix in the orbitals C (columns; row-major n x n)
     Mat g1(n2), fao(n2);
     auto evaluate = [&](const Mat &C, double &E, Mat &Fm) -> mbefci_status {
@@ -3101,6 +3130,7 @@ mbefci_status mbefci_hf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter,
     HIPCHK(hipMemcpyAsync(d_U, Uc.data(), 8 * n2, hipMemcpyHostToDevice, ctx->stream));
     hipError_t e = launch_rotate_integrals(d_h0, d_eri0, d_U, ctx->d_h, ctx->d_eri, d_tmp, n, ctx->stream);
     if (e != hipSuccess) return ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
+    trial.host = true;
     HIPCHK(hipMemcpyAsync(ctx->h.data(), ctx->d_h, 8 * n2, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipMemcpyAsync(ctx->eri.data(), ctx->d_eri, 8 * n4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
@@ -3110,6 +3140,7 @@ mbefci_status mbefci_hf(mbefci_ctx *ctx, void *ws, size_t wsb, int32_t max_iter,
             ctx->h[(size_t)p * n + q] = ctx->h[(size_t)q * n + p] = v;
         }
     HIPCHK(hipMemcpy(ctx->d_h, ctx->h.data(), 8 * n2, hipMemcpyHostToDevice));
+    trial.done();
     ctx->sym_checked = false;
     if (U_out) std::memcpy(U_out, Uc.data(), 8 * n2);
     if (e_out) *e_out = E;
