@@ -143,6 +143,9 @@ __global__ __launch_bounds__(kCcsThreads, 4) void k_ccsd_lds(CcsArgs A) {
         ob += act[k] < A.nbeta;
     }
     __shared__ CcsShape S;   // (in LDS: its arrays are indexed by the spin class)
+    static_assert(sizeof(sact) + sizeof(score) + sizeof(sh) + sizeof(Bm) + sizeof(Mm) + sizeof(xs) + sizeof(coef) +
+                      sizeof(bad_sh) + sizeof(S) + 16 <= kCcsStaticLds && kCcsMaxLds + kCcsStaticLds <= 160 * 1024,
+                  "static LDS of k_ccsd_lds");
     if (tid == 0) S.init(nA, oa, ob);
     __syncthreads();
     const int va = S.va, vb = S.vb, o = oa + ob, v = va + vb, P = S.P, n0 = S.n0;

@@ -273,6 +273,7 @@ hipError_t launch_ccsd(const double *h, const double *eri, int n, const int32_t 
 // doubles of its DIIS history in the workspace, and the launch (lds: the
 // largest of the launch's tuples)
 constexpr size_t kCcsMaxLds = 158 * 1024;
+constexpr size_t kCcsStaticLds = 1792;   // the kernel's own arrays besides them (ccs.hip checks the sum)
 size_t ccs_lds_bytes(int nA, int oa, int ob);
 int64_t ccs_history_doubles(int nA, int oa, int ob);
 hipError_t launch_ccsd_lds(const double *h, const double *eri, int n, const int32_t *act, const int32_t *nact,

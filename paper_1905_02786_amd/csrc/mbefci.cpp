@@ -1495,7 +1495,7 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
                 ob += tuples[t * k + i] < ctx->nbeta;
             }
             const size_t lds = a <= kMaxActive ? ccs_lds_bytes(a, oa, ob) : (size_t)-1;
-            const int q = lds <= kCcsMaxLds / 2 ? 0 : (lds <= kCcsMaxLds ? 1 : 2);
+            const int q = lds == (size_t)-1 || lds > kCcsMaxLds ? 2 : (lds + kCcsStaticLds <= 80 * 1024 ? 0 : 1);
             bin[q].push_back(t);
             if (q == 2) continue;
             lds_max[q] = std::max(lds_max[q], lds);
