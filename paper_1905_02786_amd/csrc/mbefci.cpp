@@ -1516,17 +1516,22 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
     double *d_out = cv.take<double>((size_t)nt);
     if (!cv.ok) return ctx->fail(MBEFCI_ENOMEM, "workspace too small for the base-model energies");
     if (model >= 2) {
-        // Tuples that fit in LDS: one workgroup each.  The larger ones: one
-        // workspace slice per tuple of a launch; when a call holds few of them
-        // (fewer than a quarter of the workgroups one cooperative launch
-        // gets), those of at least kCcCoopActive active orbitals run one at a
-        // time on many workgroups (a cooperative launch, typically the base
-        // energy of the whole space), otherwise every tuple runs batched, one
-        // workgroup each, with slices sized for the largest
+        // Tuples that fit in LDS: one workgroup each.  The larger ones (11 and
+        // more active orbitals): one workspace slice per tuple of a launch;
+        // when a call holds few tuples (fewer than a quarter of the workgroups
+        // one cooperative launch gets), these run one at a time on many
+        // workgroups (a cooperative launch, typically the base energy of the
+        // whole space), otherwise batched, one workgroup each, with slices
+        // sized for the largest.  All tuples of the call count: a cooperative
+        // launch takes 20 ms at (8e,8e) in 11 orbitals and 33 ms at (3e,3e) in
+        // 12, a batched one of 56 and 84 tuples 36 and 76 ms, so a list of
+        // which only some are large must not run those one by one (56 of 112
+        // tuples: 1040 ms so, 40 ms batched).  By the same figures the line
+        // itself, taken from smaller tuples, lies too high: the times cross at
+        // two to three tuples past LDS.
         const int coop_wgs = ccsd_coop_wgs();
         const int64_t first = nlds[0] + nlds[1];
-        const bool few = (nt - first) * 4 < coop_wgs;
-        auto coop = [&](int64_t t) { return few && na[t] >= kCcCoopActive; };
+        const bool coop = nt * 4 < coop_wgs;
         int omax = 0, vmax = 0;
         int64_t big_slice = 0;
         for (int64_t t = first; t < nt; ++t) {
@@ -1534,7 +1539,7 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
             for (int i = 0; i < na[t]; ++i) o += (act[(size_t)t * n + i] < ctx->nalpha) + (act[(size_t)t * n + i] < ctx->nbeta);
             if (na[t] > kCcMaxActive)
                 return ctx->fail(MBEFCI_EINVAL, "coupled-cluster base: more than 32 active orbitals in a tuple");
-            if (coop(t)) {
+            if (coop) {
                 big_slice = std::max(big_slice, cc_slice_doubles(o, 2 * na[t] - o));
             } else {
                 omax = std::max(omax, o);
@@ -1568,14 +1573,13 @@ mbefci_status base_energies(mbefci_ctx *ctx, int k, int64_t nt, const int16_t *t
                                     ctx->nalpha, ctx->nbeta, ctx->e_const, cnt, lds_max[q], d_work, slice, model == 3,
                                     kCcMaxIter, kCcTol, d_out + t0, d_st + t0, ctx->stream);
                 t0 += cnt;
-            } else if (coop(t0)) {
+            } else if (coop) {
                 e = launch_ccsd_coop(ctx->d_h, ctx->d_eri, n, d_act + t0 * n, d_na + t0, d_core + t0 * n, d_nc + t0, n,
                                      ctx->nalpha, ctx->nbeta, ctx->e_const, d_work, big_slice, model == 3, kCcMaxIter,
                                      kCcTol, d_out + t0, d_st + t0, wgs, d_part, ctx->stream);
                 ++t0;
             } else {
-                int cnt = 0;   // a run of small tuples
-                while (t0 + cnt < nt && cnt < per && !coop(t0 + cnt)) ++cnt;
+                const int cnt = (int)std::min<int64_t>(per, nt - t0);
                 e = launch_ccsd(ctx->d_h, ctx->d_eri, n, d_act + t0 * n, d_na + t0, d_core + t0 * n, d_nc + t0, n,
                                 ctx->nalpha, ctx->nbeta, ctx->e_const, cnt, d_work, slice, model == 3, kCcMaxIter,
                                 kCcTol, d_out + t0, d_st + t0, ctx->stream);
