@@ -255,8 +255,7 @@ constexpr int kCcMaxActive = 32;        // active orbitals of a tuple (the whole
 constexpr int kCcMaxIter = 300;         // amplitude iterations
 constexpr double kCcTol = 1e-11;        // largest amplitude change at convergence
 constexpr double kCanonTol = 1e-10;     // off-diagonal Fock elements allowed with (T)
-constexpr int kCcCoopActive = 10;       // larger tuples (past LDS) of at least this many active orbitals: one cooperative launch each
-constexpr int kCcMaxWgs = 256;          // workgroups of such a launch
+constexpr int kCcMaxWgs = 256;          // workgroups of a cooperative launch (few tuples past LDS)
 int64_t cc_slice_doubles(int o, int v);
 int ccsd_coop_wgs();
 hipError_t launch_ccsd_coop(const double *h, const double *eri, int n, const int32_t *act, const int32_t *nact,
@@ -268,10 +267,15 @@ hipError_t launch_ccsd(const double *h, const double *eri, int n, const int32_t 
                        int ntup, double *work, int64_t slice, int triples, int max_iter, double tol, double *out,
                        int32_t *status, hipStream_t s);
 
-// the same for tuples whose arrays fit in LDS (ccs.hip; every tuple of at most
-// 11 active orbitals): LDS of a tuple of nA orbitals with oa, ob occupied,
-// doubles of its DIIS history in the workspace, and the launch (lds: the
-// largest of the launch's tuples)
+// the same for tuples whose arrays fit in LDS (ccs.hip): every tuple of at most
+// 10 active orbitals, 66 of the 78 electron counts at 11 (not those with eight
+// or more occupied of both spins or at most one electron), a few at 12.  One
+// workgroup each is the faster also for a single tuple: CCSD of (5e,5e) in 10
+// orbitals 2.9 ms against 17.3 ms as one cooperative launch, (2e,2e) 1.4
+// against 13.9, (5e,5e) in 11 orbitals 4.3 against 19.6, (6e,5e) 5.6 against
+// 27.0.  LDS of a tuple of nA orbitals with oa, ob occupied, doubles of its
+// DIIS history in the workspace, and the launch (lds: the largest of the
+// launch's tuples)
 constexpr size_t kCcsMaxLds = 158 * 1024;
 constexpr size_t kCcsStaticLds = 1792;   // the kernel's own arrays besides them (ccs.hip checks the sum)
 size_t ccs_lds_bytes(int nA, int oa, int ob);
