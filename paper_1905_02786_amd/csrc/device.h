@@ -48,6 +48,12 @@ __device__ __forceinline__ const double *vref(const VecRef &r, int t, int64_t di
     return r.base + (int64_t)t * r.tstride + (int64_t)k * dim;
 }
 
+// Parity of the occupied orbitals of string m strictly between p and q.
+__device__ __forceinline__ int odd_between(uint32_t m, int p, int q) {
+    const int lo = p < q ? p : q, hi = p < q ? q : p;
+    return __popc(m & ((1u << hi) - 1u) & ~((2u << lo) - 1u)) & 1;
+}
+
 // E_core of tuple t where sigma is to hold H's full action (ecore), else 0.
 __device__ __forceinline__ double core_shift(const Batch &b, int t, int ecore) {
     return ecore ? b.params[(int64_t)t * b.pl.stride + b.pl.off_ecore] : 0.0;

@@ -206,7 +206,7 @@ inline bool sigma_fuses_dots(const Batch &b) { return b.sigma_variant == SIGMA_S
 int gemm_blocks(const Batch &b);
 hipError_t launch_guess(const Batch &b, hipStream_t s);
 hipError_t launch_init_state(const Batch &b, hipStream_t s);
-hipError_t launch_dots(const Batch &b, VecRef y, int nx_extra, hipStream_t s);
+hipError_t launch_dots(const Batch &b, VecRef y, hipStream_t s);
 // start of an iteration: the new column of the projected matrix from nsum
 // partial blocks (sd: and the S-dots of k_ritz), its lowest eigenpair, then
 // residual, correction and convergence

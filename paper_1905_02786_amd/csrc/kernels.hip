@@ -309,10 +309,7 @@ __device__ __forceinline__ int single_pair(uint32_t mi, uint32_t mj) {
 // orbitals strictly between the two.
 __device__ __forceinline__ double excitation_sign(uint32_t mi, uint32_t mj) {
     const uint32_t diff = mi ^ mj;
-    const int p = __ffs(mi & diff) - 1, q = __ffs(mj & diff) - 1;
-    const int lo = p < q ? p : q, hi = p < q ? q : p;
-    const uint32_t between = mj & (((1u << hi) - 1u) & ~((1u << (lo + 1)) - 1u));
-    return (__popc(between) & 1) ? -1.0 : 1.0;
+    return odd_between(mj, __ffs(mi & diff) - 1, __ffs(mj & diff) - 1) ? -1.0 : 1.0;
 }
 
 // H_PP[i][j] = H_a[Ia][Ja] d(Ib,Jb) + H_b[Ib][Jb] d(Ia,Ja)
@@ -1019,12 +1016,12 @@ hipError_t launch_init_state(const Batch &b, hipStream_t s) {
     return hipGetLastError();
 }
 
-// partial dots V_i . y for i < m[t] + nx_extra (running tuples only)
+// partial dots V_i . y for i <= m[t] (running tuples only)
 template <int MS>
-__global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref, int nx_extra) {
+__global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref) {
     const int t = blockIdx.y;
     if (b.status[t] != ST_RUNNING) return;
-    const int nx = b.m[t] + nx_extra;
+    const int nx = b.m[t] + 1;
     const double *V = b.V + (int64_t)t * b.max_space * b.dim;
     const double *y = vref(yref, t, b.dim);
     double acc[MS + 1];
@@ -1039,9 +1036,9 @@ __global__ __launch_bounds__(256) void k_dots(Batch b, VecRef yref, int nx_extra
     store_block_partials<MS + 1>(b, t, acc, nx);
 }
 
-hipError_t launch_dots(const Batch &b, VecRef y, int nx_extra, hipStream_t s) {
-    if (b.max_space <= 12) hipLaunchKernelGGL(k_dots<12>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra);
-    else hipLaunchKernelGGL(k_dots<kMaxSpace>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y, nx_extra);
+hipError_t launch_dots(const Batch &b, VecRef y, hipStream_t s) {
+    if (b.max_space <= 12) hipLaunchKernelGGL(k_dots<12>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y);
+    else hipLaunchKernelGGL(k_dots<kMaxSpace>, dim3(b.nblk, b.B), dim3(256), 0, s, b, y);
     return hipGetLastError();
 }
 

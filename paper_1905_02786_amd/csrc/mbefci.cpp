@@ -771,7 +771,7 @@ struct BatchRun {
         if ((e = launch_orthonormalize(b, st)) != hipSuccess) return e;
         if ((e = launch_sigma(b, vm(), sm(), 0, true, fused, st, nullptr, nullptr, nullptr, nullptr)) != hipSuccess)
             return e;
-        return fused ? hipSuccess : launch_dots(b, sm(), 1, st);
+        return fused ? hipSuccess : launch_dots(b, sm(), st);
     }
 
     // sigma of V_m into S_m and the partial dots of the projected matrix's new
@@ -779,7 +779,7 @@ struct BatchRun {
     mbefci_status sigma_and_dots(mbefci_ctx *ctx, int64_t napps) {
         const mbefci_status r = run_sigma(ctx, b, vm(), sm(), 0, true, napps, fused, s);
         if (r != MBEFCI_OK) return r;
-        const hipError_t e = fused ? hipSuccess : launch_dots(b, sm(), 1, s);
+        const hipError_t e = fused ? hipSuccess : launch_dots(b, sm(), s);
         return e == hipSuccess ? MBEFCI_OK : ctx->fail(MBEFCI_EDEVICE, hipGetErrorString(e));
     }
 

@@ -163,10 +163,6 @@ __global__ __launch_bounds__(256) void k_build_h(Batch b, int beta, int rows) {
     }
     __syncthreads();
     auto pair = [](int p, int q) { return p > q ? p * (p + 1) / 2 + q : q * (q + 1) / 2 + p; };
-    auto odd = [](uint32_t m, int p, int q) {   // occupied orbitals of m strictly between p and q
-        const int lo = p < q ? p : q, hi = p < q ? q : p;
-        return __popc(m & ((1u << hi) - 1u) & ~((2u << lo) - 1u)) & 1;
-    };
     const uint32_t r0 = (uint32_t)blockIdx.x * rows, r1 = min(r0 + (uint32_t)rows, N);
     double *H = (beta ? b.Hb : b.Ha) + (int64_t)t * N * N;
     for (uint32_t row = r0 + wv; row < r1; row += 4) {
@@ -180,7 +176,7 @@ __global__ __launch_bounds__(256) void k_build_h(Batch b, int beta, int rows) {
                 const int p1 = __ffs(cr) - 1, p2 = 31 - __clz(cr), q1 = __ffs(an) - 1, q2 = 31 - __clz(an);
                 const uint32_t mk = mj ^ (1u << q2) ^ (1u << p2);   // E_{p2 q2} J
                 v = 2.0 * (eri[pair(p1, q1) * ld + pair(p2, q2)] - eri[pair(p1, q2) * ld + pair(p2, q1)]);
-                if (odd(mj, p2, q2) ^ odd(mk, p1, q1)) v = -v;
+                if (odd_between(mj, p2, q2) ^ odd_between(mk, p1, q1)) v = -v;
             } else if (nd == 2) {
                 const int p = __ffs(mi & diff) - 1, q = __ffs(mj & diff) - 1, pq = pair(p, q);
                 const uint32_t both = mi & mj;
@@ -190,7 +186,7 @@ __global__ __launch_bounds__(256) void k_build_h(Batch b, int beta, int rows) {
                     if ((both >> r) & 1u) v += 2.0 * eri[pq * ld + r * (r + 3) / 2] - x;
                     else v += x;
                 }
-                if (odd(mj, p, q)) v = -v;
+                if (odd_between(mj, p, q)) v = -v;
             } else if (nd == 0) {
                 for (int i = 0; i < nA; ++i)
                     if ((mi >> i) & 1u) {
