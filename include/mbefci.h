@@ -168,7 +168,7 @@ typedef struct {
     int32_t whole_dim;      /* whole-tuple mode: with profile = 0, shape classes of at most this many
                                determinants (0..4900, default 1225; 0: off) and at most 10 active
                                orbitals run each tuple's whole Davidson solve in one workgroup of a
-                               single launch (the batched path launches a dozen kernels per
+                               single launch (the batched path launches about eight kernels per
                                iteration); their P space is at most 32 determinants unless it holds
                                the whole CAS.  Above about 1225 determinants the batched path's
                                MFMA sigma is faster.  Same energies within the tolerances. */
@@ -294,8 +294,13 @@ mbefci_status mbefci_set_options(mbefci_ctx *ctx, const mbefci_options *opt);
 
 /* Device bytes needed to solve the given tuples: *min_bytes holds the
  * largest single tuple (one at a time), *want_bytes every tuple of the largest
- * shape class in one batch.  tuples: host int16, ntup rows of `order`
- * ascending expansion orbitals. */
+ * shape class in one batch.  More is of use where a list has several classes:
+ * those that fit side by side, each in one batch, run at the same time (up to
+ * eight).  Two to four times *want_bytes hold most of them: 24 orbitals, orders
+ * 0 to 3, 31.9 ms with the largest *want_bytes of the orders (815 MiB), 27.2
+ * with twice and 24.7 with four times that, as with 8 GiB; 10 orbitals, full
+ * order, 22.5 (18 MiB), 14.2 and 14.2 ms.  tuples: host int16, ntup rows of
+ * `order` ascending expansion orbitals. */
 mbefci_status mbefci_workspace_query(mbefci_ctx *ctx, int32_t order, int64_t ntup,
                                      const int16_t *tuples, size_t *min_bytes,
                                      size_t *want_bytes);

@@ -6,7 +6,7 @@
 // multiply-adds per iteration once spin and antisymmetry are used; the
 // spin-orbital loops over L2-resident N^4 arrays that this replaces did thirty
 // times that and waited for a load at every term (680 order-3 tuples of 24
-// orbitals: 70 ms; now 8.0 ms).  So:
+// orbitals: 70 ms; now 7.0 ms).  So:
 //  * T2 is kept for i < j, a < b and the spin classes aa, ab, bb only: a
 //    matrix (occupied pair) x (virtual pair) per class.  The ladder terms are
 //    products of such matrices with W_abef and W_mnij, class by class.

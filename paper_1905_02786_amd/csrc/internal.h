@@ -232,10 +232,15 @@ hipError_t launch_rdm_embed(const Batch &b, const double *w, double *gh, double 
 // and kWholeMaxActive orbitals, with the vector of each sigma, the pair
 // integrals, the string Hamiltonians and both link tables in LDS
 constexpr int kWholeMaxDim = 4900;
-constexpr int kWholeDefaultDim = 1225;   // default options.whole_dim (measured crossover)
+// Default options.whole_dim: where the mode and the batched iteration take the
+// same time.  One class of 16, 64, 256 and 700 tuples, batched against whole:
+// 400 determinants 1.3, 1.4, 1.7, 2.8 against 0.7, 0.7, 0.9, 1.8 ms; 784 1.7,
+// 1.8, 2.1, 3.8 against 1.4, 1.5, 1.6, 3.6; 1225 1.8, 2.0, 2.5, 4.2 against
+// 2.0, 2.0, 2.1, 4.3.
+constexpr int kWholeDefaultDim = 1225;
 constexpr int kWholeMaxActive = 10;
-constexpr int kWholeMaxNent = 32;
-constexpr int kWholePsp = 32;      // P space of the whole-tuple mode (at most options.pspace)   // link entries per string (n (n_A - n + 1) <= 30 for n_A <= 10)
+constexpr int kWholeMaxNent = 32;  // link entries per string (n (n_A - n + 1) <= 30 for n_A <= 10)
+constexpr int kWholePsp = 32;      // P space of the whole-tuple mode (at most options.pspace)
 // (same: both spins have the same electron count and share one string Hamiltonian)
 bool whole_fits(const ParamLayout &pl, int64_t dim, int64_t Na, int64_t Nb, int nentA, int nentB, bool same);
 // after the set-up (gather, string Hamiltonians, diagonal, P space, guess):
