@@ -46,10 +46,10 @@ KERNEL_NAMES = {0: "k_sigma_strip", 1: "k_sigma_linked_gat", 2: "k_sigma_linked_
 TRAFFIC = {
     # kernel id -> (sources sha1, calibrated bytes per application), from
     # profiles/hbm-traffic-large-n60-order4.md
-    "large": {3: ("675a88d92d522c96cf5ab739ee9f1113a8d70f44", 7057598.9),
-              5: ("675a88d92d522c96cf5ab739ee9f1113a8d70f44", 253413248.1)},
+    "large": {3: ("e0699297378398c14e937faf51546ed4de7c70d9", 7057598.9),
+              5: ("e0699297378398c14e937faf51546ed4de7c70d9", 253413248.1)},
     # profiles/hbm-traffic-sweep-n24-cas66-orders1-5.md
-    "sweep": {2: ("675a88d92d522c96cf5ab739ee9f1113a8d70f44", 1423796.7)},
+    "sweep": {2: ("e0699297378398c14e937faf51546ed4de7c70d9", 1423796.7)},
 }
 
 

@@ -66,7 +66,7 @@ __device__ __forceinline__ void link_decode(uint32_t L, int &J, int &Q, double &
 }
 
 // Block partials of tuple t: [B][nblk + 1][kParts] (the extra block holds the
-// P-space corrections of the Davidson reductions).
+// P-space correction of the guess's norm).
 __device__ __forceinline__ double *parts(const Batch &b, int t, int blk) {
     return b.part + ((int64_t)t * (b.nblk + 1) + blk) * kParts;
 }

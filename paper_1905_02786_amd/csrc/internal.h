@@ -112,7 +112,7 @@ struct Batch {
     double *W;              // [B][P][dim] sigma intermediate (SIGMA_WMAT)
     double *Ha, *Hb;        // [B][Na][Na], [B][Nb][Nb] string Hamiltonians (SIGMA_STRIP; Ha == Hb when na == nb)
     int nblk;               // blocks per tuple for vector kernels
-    double *part;           // [B][nblk + 1][kParts] block partial sums (the last block: P-space corrections)
+    double *part;           // [B][nblk + 1][kParts] block partial sums (the last block: P-space part of the guess's norm)
     double *G;              // [B][kMaxSpace*kMaxSpace] projected matrix Q^T H Q (below)
     // The stored basis V is not orthonormal: V = Q U with Q orthonormal and U
     // upper triangular; R = U^-1 (upper triangular, R[i][j] at i*kMaxSpace+j,

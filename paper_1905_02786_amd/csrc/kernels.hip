@@ -156,7 +156,7 @@ __device__ double sum_parts(const Batch &b, int t, int i) {
     return s;
 }
 
-// the same plus the P-space correction block (guess norm, Ritz partials)
+// the same plus the P-space correction block (guess norm)
 __device__ double sum_parts_x(const Batch &b, int t, int i) {
     const double s = sum_parts(b, t, i);
     return b.psp > 0 ? s + parts(b, t, b.nblk)[i] : s;
